@@ -191,11 +191,13 @@ ar_status ar_plan_destroy(ar_plan* plan);
  * reaches that point every buffer holds the AllReduce result, bit for bit
  * the result of running the steps phase by phase as listed.  The
  * pointer array is read during the call only.  Any pointer alignment works;
- * 16-byte-aligned buffers take the vector path.  The first call on a device
- * uploads the plan's tile tables; the first call with a new buffer set
- * builds that set's step records (each executed step's range and resolved
- * buffer pointers, (4 + k + d) * 8 bytes rounded up to 16 for a step with
- * k sources and d destinations) on the host and uploads them; the plan keeps
+ * buffers at their element's alignment may run as one one-pass launch
+ * (AR_OPT_RESIDENT), otherwise 16-byte-aligned buffers take the vector path.
+ * The first call on a device uploads the plan's tile tables; the first call
+ * with a new buffer set builds that set's step records (each executed step's
+ * range and resolved buffer pointers, (4 + k + d) * 8 bytes rounded up to 16
+ * for a step with k sources and d destinations; for a one-pass launch the n
+ * pointers alone) on the host and uploads them; the plan keeps
  * the records of its 4 most recently used buffer sets per device (device and
  * pinned host memory owned by the plan), so repeated executes on the same
  * buffers only launch kernels.  Such a call may therefore be captured in a
@@ -276,7 +278,8 @@ ar_status ar_plan_execute_noalloc(ar_plan* plan, void* const* bufs, void* stream
  *  of any size for a resident one.  A run is possible when
  *  every boundary of its steps is a multiple of 16 bytes; sliced launches
  *  are used only with 16-byte aligned buffers (otherwise every phase runs
- *  as its phase launches, those reported with AR_OPT_SLICE = 0). */
+ *  as its phase launches, those reported with AR_OPT_SLICE = 0, or with 2 the
+ *  whole plan one-pass, below). */
 /*  AR_OPT_RESIDENT (default 1): a sliced launch may run resident instead:
  *  each workgroup keeps its tile of element positions in on-chip memory
  *  (LDS) for the whole run, loading each buffer's tile once, before the
@@ -291,14 +294,25 @@ ar_status ar_plan_execute_noalloc(ar_plan* plan, void* const* bufs, void* stream
  *  the plain or the resident form per run (n <= 64), or (n > 64) runs the
  *  whole plan as one streamed launch when it predicts that faster than the
  *  runs it chose; with AR_OPT_SLICE = 1 the whole plan runs resident.
- *  0: sliced launches always run plain. */
+ *  A plan that leaves the same value in every buffer (as every built-in kind
+ *  does) may also run one-pass: one launch in which each wavefront loads its
+ *  tile of element positions from every buffer, computes that value in
+ *  registers (every step's fold on the same values in the same order, the
+ *  same bits) and stores it to every buffer, so that each position of each
+ *  buffer is read and written once.  Step boundaries and buffers may then lie
+ *  at any element.  With AR_OPT_SLICE = 2 it runs so where a step boundary or
+ *  a buffer is off 16 bytes (up to 512 buffers, beyond where predicted
+ *  faster) and elsewhere where predicted well faster; and a whole-plan sliced,
+ *  resident or streamed launch takes this form where it is the faster one.
+ *  0: sliced launches always run plain, and no launch one-pass. */
 typedef enum ar_option { AR_OPT_FUSE = 0, AR_OPT_SLICE = 1, AR_OPT_RESIDENT = 2 } ar_option;
 ar_status ar_plan_set_option(ar_plan* plan, int32_t option, int64_t value);
 
 /* The kernel launches one execution on 16-byte aligned buffers issues (host
  * only, no GPU call): their number, and for launch i the plan phase its
  * steps come from (-1 for a sliced launch, -2 for a resident one, -3 for a
- * streamed resident one), their
+ * streamed resident one; a one-pass launch counts as resident, or as the
+ * whole-plan launch whose form it is), their
  * source count (the
  * largest, for a sliced launch), the most destinations any of its
  * steps stores to, its number of steps and its algorithmic bytes:

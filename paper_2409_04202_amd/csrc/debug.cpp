@@ -188,6 +188,128 @@ static std::string check_streamed(const ar_plan& plan, const ExecState& ex, cons
 // destinations cover each destination once, the ones among the step's
 // sources (stored after the barrier) last.  An affinity table puts every
 // tile on the XCD (workgroup id modulo kNumXCDs) that xcd_of names.
+// Check of the one-pass form (onepass_kernel): per segment, running its leaves
+// on terms (an input row, an unordered 2-operand add, for bf16 the rounding at
+// the end of a fold) with the sums put aside gives the term that the executed
+// steps, phase by phase, leave in every buffer; its tiles, on buffers with
+// 16-byte alignment and without, store every element of the segment once, and
+// every vector lies within the buffers.  Returns "" or the first problem.
+static std::string check_onepass(const ar_plan& plan, const ExecState& ex) {
+    const OnePlan& one = ex.one;
+    const size_t n = size_t(plan.n);
+    const bool rounds = plan.dtype == AR_BF16;
+    const int vec = one.conf.lb / plan.esize;
+    const int64_t te = int64_t(64) * vec * one.conf.u;
+    if (plan.N < vec || one.segs.empty()) return "one-pass shape";
+    int64_t pos = 0;
+    for (const OneSeg& sg : one.segs) {
+        if (sg.lo != pos || sg.hi <= sg.lo) return "one-pass segments leave a gap or overlap";
+        pos = sg.hi;
+        if (sg.nleaf < 1 || sg.off < 0 || size_t(sg.off) + size_t(sg.nleaf) > one.prog.size())
+            return "one-pass leaves out of range";
+    }
+    if (pos != plan.N) return "one-pass segments do not cover the buffers";
+    std::vector<int64_t> cuts{0, plan.N};
+    for (const XPhase& xp : ex.phases)
+        for (const XStep& x : xp.steps)
+            if (x.end > x.begin) {
+                cuts.push_back(x.begin);
+                cuts.push_back(x.end);
+            }
+    std::sort(cuts.begin(), cuts.end());
+    cuts.erase(std::unique(cuts.begin(), cuts.end()), cuts.end());
+    for (size_t c = 0; c + 1 < cuts.size(); ++c) {
+        std::map<std::tuple<int, int64_t, int64_t>, int64_t> terms;
+        auto term = [&](int kind, int64_t x, int64_t y) {
+            if (kind == 1 && x > y) std::swap(x, y);  // add: unordered
+            return terms.emplace(std::make_tuple(kind, x, y), int64_t(terms.size())).first->second;
+        };
+        auto end = [&](int64_t t) { return rounds ? term(2, t, 0) : t; };
+        std::vector<int64_t> want(n);
+        for (size_t b = 0; b < n; ++b) want[b] = term(0, int64_t(b), 0);
+        const std::vector<int64_t> input = want;
+        for (const XPhase& xp : ex.phases) {
+            std::vector<std::pair<int32_t, int64_t>> outs;
+            for (const XStep& x : xp.steps) {
+                if (!(x.end > x.begin && x.begin <= cuts[c] && cuts[c + 1] <= x.end)) continue;
+                int64_t t = want[size_t(x.srcs[0])];
+                for (size_t j = 1; j < x.srcs.size(); ++j) t = term(1, t, want[size_t(x.srcs[j])]);
+                if (x.srcs.size() > 1) t = end(t);
+                for (int32_t d : x.dsts) outs.push_back({d, t});
+            }
+            for (const auto& o : outs) want[size_t(o.first)] = o.second;
+        }
+        size_t s = 0;
+        while (one.segs[s].hi <= cuts[c]) ++s;
+        const OneSeg& sg = one.segs[s];
+        if (sg.lo > cuts[c] || cuts[c + 1] > sg.hi) return "a step cuts a one-pass segment";
+        int64_t acc = -1;
+        std::vector<int64_t> aside;
+        for (int32_t i = 0; i < sg.nleaf; ++i) {
+            const uint32_t w = one.prog[size_t(sg.off + i)];
+            if ((w & 0xFFFFu) >= n) return "one-pass leaf out of range";
+            if (w & kOnePush) {
+                if (acc < 0) return "one-pass push of nothing";
+                aside.push_back(acc);
+                acc = -1;
+                if (int32_t(aside.size()) > one.depth) return "too many sums put aside";
+            }
+            const int64_t x = input[size_t(w & 0xFFFFu)];
+            acc = acc < 0 ? x : term(1, acc, x);
+            for (uint32_t k = w >> kOnePopShift; k; --k) {
+                if (aside.empty()) return "one-pass pop of nothing";
+                acc = term(1, aside.back(), end(acc));
+                aside.pop_back();
+            }
+            if (w & kOneRound) acc = end(acc);
+        }
+        if (!aside.empty()) return "one-pass sums left aside";
+        acc = end(acc);
+        for (size_t b = 0; b < n; ++b)
+            if (want[b] != acc) return "one-pass value of a buffer differs";
+    }
+    for (int32_t amask : {vec - 1, 0}) {
+        std::vector<std::vector<int64_t>> tiles(one.segs.size());
+        for (int64_t u = 0; u < one.nunits; ++u) {
+            int64_t s = u / one.tiles_per_seg, t = u - s * one.tiles_per_seg;
+            if (!one.tiles.empty()) {
+                s = one.tiles[size_t(u)].x;
+                t = one.tiles[size_t(u)].y;
+            }
+            if (s < 0 || s >= int64_t(one.segs.size()) || t < 0) return "one-pass tile out of range";
+            tiles[size_t(s)].push_back(t);
+        }
+        for (size_t s = 0; s < one.segs.size(); ++s) {
+            const OneSeg& sg = one.segs[s];
+            std::sort(tiles[s].begin(), tiles[s].end());
+            int64_t next = 0, at = sg.lo;
+            for (int64_t t : tiles[s]) {
+                if (t != next++) return "one-pass tiles leave a gap or overlap";
+                const int64_t t0 = one_tile(sg.lo, t, te, amask);
+                if (t0 >= sg.hi) continue;
+                if (t0 >= sg.lo && t0 + te <= sg.hi) {  // whole vectors
+                    if (t0 != at) return "one-pass tile misplaced";
+                    at = t0 + te;
+                    continue;
+                }
+                for (int64_t i = 0; i < 64 * one.conf.u; ++i) {
+                    const int64_t e = t0 + i * vec;
+                    const OneLane l = one_lane(t0, e, sg.lo, sg.hi, plan.N, vec);
+                    const int64_t back = t0 < vec ? t0 : vec;
+                    if (l.at < 0 || l.at + vec > plan.N || l.at < t0 - back)
+                        return "one-pass vector outside the buffers";
+                    if (l.fa >= l.fb) continue;
+                    if (l.fa < 0 || l.fb > vec || l.at + l.fa != at)
+                        return "one-pass elements stored twice or not at all";
+                    at = l.at + l.fb;
+                }
+            }
+            if (at != sg.hi) return "one-pass tiles do not cover a segment";
+        }
+    }
+    return "";
+}
+
 AR_EXPORT ar_status ar_debug_check_tiling(ar_plan* plan, int32_t vecok,
                                           char* msg, int64_t msglen) {
     clear_error();
@@ -327,6 +449,13 @@ AR_EXPORT ar_status ar_debug_check_tiling(ar_plan* plan, int32_t vecok,
         // segment
         {
             std::vector<int32_t> slice_of(ex->phases.size(), -1);
+            if (ex->one_unaligned) build_onepass(*plan, *ex, ex->one);
+            if (ex->one.ok) {
+                const std::string e = check_onepass(*plan, *ex);
+                if (!e.empty()) return bad(e);
+            } else if (ex->one_aligned) {
+                return bad("one-pass route without its form");
+            }
             int32_t prev_end = 0;
             for (size_t k = 0; k < ex->slices.size(); ++k) {
                 const SliceDesc& sd = ex->slices[k];
@@ -337,7 +466,7 @@ AR_EXPORT ar_status ar_debug_check_tiling(ar_plan* plan, int32_t vecok,
                 for (int32_t q = sd.p0; q < prev_end; ++q) slice_of[size_t(q)] = int32_t(k);
             }
             std::vector<int32_t> runs_of(ex->launches.size(), 0), seen(ex->slices.size(), 0);
-            for (const Stage& stg : ex->stages) {
+            for (const Stage& stg : ex->run_stages) {
                 if (stg.slice >= 0) {
                     if (stg.slice >= int32_t(ex->slices.size())) return bad("stage names no slice");
                     ++seen[size_t(stg.slice)];
@@ -693,6 +822,7 @@ AR_EXPORT ar_status ar_debug_launch_desc(ar_plan* plan, int32_t stage, int64_t* 
         if (stage < 0 || stage >= int32_t(ex->stages.size()))
             return fail(AR_ERR_INVALID_ARG, "launch index out of range");
         const Stage stg = ex->stages[size_t(stage)];
+        if (stg.slice < 0 && stg.launch < 0) return fail(AR_ERR_INVALID_ARG, "a one-pass launch");
         if (stg.slice >= 0) return fail(AR_ERR_INVALID_ARG, "a sliced launch");
         const LaunchDesc& L = ex->launches[size_t(stg.launch)];
         out[0] = L.kern_k;

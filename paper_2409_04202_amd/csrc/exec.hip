@@ -50,14 +50,19 @@ static void free_dev(DevState* d) {
     if (d->stiles) (void)hipFree(d->stiles);
     if (d->runits) (void)hipFree(d->runits);
     if (d->prog) (void)hipFree(d->prog);
-    for (PtrEntry& e : d->cache) {
-        if (e.done) {
-            (void)hipEventSynchronize(e.done);
-            (void)hipEventDestroy(e.done);
+    if (d->one_segs) (void)hipFree(d->one_segs);
+    if (d->one_prog) (void)hipFree(d->one_prog);
+    if (d->one_tiles) (void)hipFree(d->one_tiles);
+    for (PtrEntry* c : {d->cache, d->one_cache})
+        for (int i = 0; i < kCache; ++i) {
+            PtrEntry& e = c[i];
+            if (e.done) {
+                (void)hipEventSynchronize(e.done);
+                (void)hipEventDestroy(e.done);
+            }
+            if (e.dev) (void)hipFree(e.dev);
+            if (e.pinned) (void)hipHostFree(e.pinned);
         }
-        if (e.dev) (void)hipFree(e.dev);
-        if (e.pinned) (void)hipHostFree(e.pinned);
-    }
     if (cur >= 0) (void)hipSetDevice(cur);
     delete d;
 }
@@ -80,7 +85,11 @@ static ar_status upload(T** dst, const std::vector<T>& src, const char* what) {
                     hip_msg(what, e));
     }
     e = hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return fail(AR_ERR_HIP, hip_msg(what, e));
+    if (e != hipSuccess) {
+        (void)hipFree(*dst);
+        *dst = nullptr;
+        return fail(AR_ERR_HIP, hip_msg(what, e));
+    }
     return AR_OK;
 }
 
@@ -107,32 +116,40 @@ static SliceTables slice_tables(const ExecState& ex) {
     return t;
 }
 
-static ar_status device_state(Plan& p, ExecState& ex, DevState** out) {
+// The plan's state on the current device, with the tables of the route a
+// call takes (`one`: the one-pass launch's).
+static ar_status device_state(Plan& p, ExecState& ex, bool one, DevState** out) {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail(AR_ERR_HIP, hip_msg("hipGetDevice", e));
     if (dev < 0) return fail(AR_ERR_HIP, "no current device");
     if (size_t(dev) >= ex.dev.size()) ex.dev.resize(size_t(dev) + 1, nullptr);
     if (!ex.dev[size_t(dev)]) {
-        DevState* d = new DevState();
-        d->device = dev;
-        ar_status s = upload(&d->tiles, ex.htiles, "tile table");
+        ex.dev[size_t(dev)] = new DevState();
+        ex.dev[size_t(dev)]->device = dev;
+    }
+    DevState* d = ex.dev[size_t(dev)];
+    ar_status s = AR_OK;
+    if (one && !d->one) {
+        if (!d->one_segs) s = upload(&d->one_segs, ex.one.segs, "one-pass segments");
+        if (s == AR_OK && !d->one_prog) s = upload(&d->one_prog, ex.one.prog, "one-pass leaves");
+        if (s == AR_OK && !d->one_tiles) s = upload(&d->one_tiles, ex.one.tiles, "one-pass tiles");
+        d->one = s == AR_OK;
+    } else if (!one && !d->staged) {
+        if (!d->tiles) s = upload(&d->tiles, ex.htiles, "tile table");
         if (s == AR_OK && !ex.slices.empty()) {
             const SliceTables t = slice_tables(ex);
-            s = upload(&d->cuts, t.cuts, "segment table");
-            if (s == AR_OK) s = upload(&d->sched_off, t.soff, "schedule offsets");
-            if (s == AR_OK) s = upload(&d->sched, t.sched, "schedule");
-            if (s == AR_OK) s = upload(&d->stiles, t.tiles, "slice tiles");
-            if (s == AR_OK) s = upload(&d->runits, t.runits, "resident units");
-            if (s == AR_OK) s = upload(&d->prog, t.prog, "resident programs");
+            if (!d->cuts) s = upload(&d->cuts, t.cuts, "segment table");
+            if (s == AR_OK && !d->sched_off) s = upload(&d->sched_off, t.soff, "schedule offsets");
+            if (s == AR_OK && !d->sched) s = upload(&d->sched, t.sched, "schedule");
+            if (s == AR_OK && !d->stiles) s = upload(&d->stiles, t.tiles, "slice tiles");
+            if (s == AR_OK && !d->runits) s = upload(&d->runits, t.runits, "resident units");
+            if (s == AR_OK && !d->prog) s = upload(&d->prog, t.prog, "resident programs");
         }
-        if (s != AR_OK) {
-            free_dev(d);
-            return s;
-        }
-        ex.dev[size_t(dev)] = d;
+        d->staged = s == AR_OK;
     }
-    *out = ex.dev[size_t(dev)];
+    if (s != AR_OK) return s;
+    *out = d;
     (void)p;
     return AR_OK;
 }
@@ -162,6 +179,18 @@ static bool buffers_aligned(void* const* bufs, int32_t n) {
     return true;
 }
 
+// Does a call on these buffers run the one-pass launch?  (Its form is built
+// here when only unaligned buffers take it.)
+static bool takes_one(const Plan& p, ExecState& ex, void* const* bufs) {
+    if (!ex.one_aligned && !ex.one_unaligned) return false;
+    if (buffers_aligned(bufs, p.n)) return ex.one_aligned;
+    if (!ex.one_unaligned) return false;
+    for (int32_t i = 0; i < p.n; ++i)  // each at its element's alignment
+        if (reinterpret_cast<uint64_t>(bufs[i]) & uint64_t(p.esize - 1)) return false;
+    build_onepass(p, ex, ex.one);
+    return ex.one.ok;
+}
+
 // The step records of buffer set bufs[0..n) (see StepHead) followed by the n
 // buffer pointers, written to w[0 .. rec_words + n).
 static void fill_records(const ExecState& ex, void* const* bufs, int32_t n, uint64_t* w) {
@@ -181,26 +210,27 @@ static void fill_records(const ExecState& ex, void* const* bufs, int32_t n, uint
 }
 
 // The step records for buffer set `bufs` on this device (see StepHead),
-// followed by the n buffer pointers: from the per-plan cache, or built on
-// the host and uploaded on `stream`.
+// followed by the n buffer pointers (`one`: the pointers alone): from the
+// per-plan cache, or built on the host and uploaded on `stream`.
 static ar_status step_records(const Plan& p, const ExecState& ex, DevState& d,
-                              const std::vector<void*>& bufs,
+                              const std::vector<void*>& bufs, bool one,
                               hipStream_t stream, PtrEntry** out) {
+    PtrEntry* const cache = one ? d.one_cache : d.cache;
     ++d.clock;
-    for (PtrEntry& e : d.cache)
-        if (e.valid && e.key == bufs) {
-            e.stamp = d.clock;
-            *out = &e;
+    for (int i = 0; i < kCache; ++i)
+        if (cache[i].valid && cache[i].key == bufs) {
+            cache[i].stamp = d.clock;
+            *out = &cache[i];
             return AR_OK;
         }
     ar_status s = check_buffers(p, bufs);
     if (s != AR_OK) return s;
-    PtrEntry* v = &d.cache[0];
-    for (PtrEntry& e : d.cache) {
-        if (!e.valid) { v = &e; break; }
-        if (e.stamp < v->stamp) v = &e;
+    PtrEntry* v = &cache[0];
+    for (int i = 0; i < kCache; ++i) {
+        if (!cache[i].valid) { v = &cache[i]; break; }
+        if (cache[i].stamp < v->stamp) v = &cache[i];
     }
-    const size_t nb = size_t(ex.rec_words + p.n) * sizeof(uint64_t);
+    const size_t nb = size_t((one ? 0 : ex.rec_words) + p.n) * sizeof(uint64_t);
     hipError_t e = hipSuccess;
     if (!v->dev) {
         e = hipMalloc(reinterpret_cast<void**>(&v->dev), nb);
@@ -226,7 +256,8 @@ static ar_status step_records(const Plan& p, const ExecState& ex, DevState& d,
         if (e != hipSuccess) return fail(AR_ERR_HIP, hip_msg("hipEventSynchronize", e));
     }
     v->valid = false;
-    fill_records(ex, bufs.data(), p.n, v->pinned);
+    if (one) std::memcpy(v->pinned, bufs.data(), nb);
+    else fill_records(ex, bufs.data(), p.n, v->pinned);
     e = hipMemcpyAsync(v->dev, v->pinned, nb, hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return fail(AR_ERR_HIP, hip_msg("step record upload", e));
     e = hipEventRecord(v->done, stream);
@@ -334,7 +365,41 @@ struct DevView {
     const uint32_t* prog;
     const uint64_t* recs;  // step records, then the n buffer pointers
     bool aligned;          // every buffer 16-byte aligned
+    // the one-pass launch, when the call takes it: its tables, the pointers
+    bool one = false;
+    const OneSeg* one_segs = nullptr;
+    const uint32_t* one_prog = nullptr;
+    const int2* one_tiles = nullptr;
+    const uint64_t* ptrs = nullptr;
 };
+
+template <int DT, int LB, int U, int B, int W>
+static void launch_one(const Plan& p, const OnePlan& one, const DevView& v, hipStream_t stream) {
+    const int64_t blocks = (one.nunits + W - 1) / W;
+    const uint32_t per_xcd = static_cast<uint32_t>((blocks + 7) / 8);
+    const dim3 grid(per_xcd * 8), block(64 * W);
+    const size_t lds = size_t(one.depth) * U * 64 * W * sizeof(typename OneVec<DT, LB>::Acc);
+    const int32_t amask = v.aligned ? LB / p.esize - 1 : 0;
+#define AR_ONE(CM)                                                                            \
+    hipLaunchKernelGGL((onepass_kernel<DT, LB, U, B, W, CM>), grid, block, lds, stream, v.ptrs,   \
+                       p.n, v.one_prog, v.one_segs, int32_t(one.segs.size()), v.one_tiles,    \
+                       uint32_t(one.nunits), uint32_t(one.tiles_per_seg), per_xcd, p.N, amask)
+    if (one.cm == 3) AR_ONE(3);
+    else AR_ONE(0);
+#undef AR_ONE
+}
+
+template <int DT>
+static void launch_one_d(const Plan& p, const OnePlan& one, const DevView& v, hipStream_t stream) {
+    switch (one.conf.kind) {
+        case ONE_LB4: launch_one<DT, 4, 1, 32, 4>(p, one, v, stream); break;
+        case ONE_U4: launch_one<DT, 16, 4, 4, 1>(p, one, v, stream); break;
+        case ONE_U16: launch_one<DT, 16, 16, 1, 1>(p, one, v, stream); break;
+        case ONE_U1B4: launch_one<DT, 16, 1, 4, 1>(p, one, v, stream); break;
+        case ONE_U1B8: launch_one<DT, 16, 1, 8, 1>(p, one, v, stream); break;
+        default: launch_one<DT, 16, 1, 16, 1>(p, one, v, stream); break;
+    }
+}
 
 // Enqueue the launches of one execution on `stream`.
 static ar_status launch_all(ar_plan* plan, const ExecState* ex, const DevView& v,
@@ -345,7 +410,8 @@ static ar_status launch_all(ar_plan* plan, const ExecState* ex, const DevView& v
         // sliced launches need 16-byte aligned buffers; otherwise every
         // phase runs as its phase launches
         const bool staged = v.aligned;
-        const int64_t nlaunch = staged ? int64_t(ex->stages.size()) : int64_t(ex->launches.size());
+        const int64_t nlaunch = v.one ? 1
+                                : staged ? int64_t(ex->run_stages.size()) : int64_t(ex->launches.size());
         if (timer && timer->count + nlaunch > timer->cap)
             return fail(AR_ERR_INVALID_ARG, "timer is full");
         auto mark = [&](int j) -> ar_status {  // event j (0 begin, 1 end) of this record
@@ -365,8 +431,15 @@ static ar_status launch_all(ar_plan* plan, const ExecState* ex, const DevView& v
         for (int64_t li = 0; li < nlaunch; ++li) {
             s = mark(0);
             if (s != AR_OK) return s;
-            const Stage stg = staged ? ex->stages[size_t(li)] : Stage{-1, int32_t(li)};
-            if (stg.slice >= 0 && ex->slices[size_t(stg.slice)].streamed) {
+            const Stage stg = v.one    ? Stage{-1, -1}
+                              : staged ? ex->run_stages[size_t(li)] : Stage{-1, int32_t(li)};
+            if (v.one) {
+                switch (plan->dtype) {
+                    case AR_F32: launch_one_d<DT_F32>(*plan, ex->one, v, stream); break;
+                    case AR_I32: launch_one_d<DT_I32>(*plan, ex->one, v, stream); break;
+                    default: launch_one_d<DT_BF16>(*plan, ex->one, v, stream); break;
+                }
+            } else if (stg.slice >= 0 && ex->slices[size_t(stg.slice)].streamed) {
                 const SliceDesc& sd = ex->slices[size_t(stg.slice)];
                 if (sd.res_waves != 4) return fail(AR_ERR_INTERNAL, "streamed launch shape");
                 const dim3 grid(static_cast<uint32_t>(sd.nunits)), block(256);
@@ -465,14 +538,22 @@ static ar_status run(ar_plan* plan, const std::vector<void*>& bufs,
         if (plan->N == 0 || plan->num_phases() == 0) return AR_OK;
         ExecState* ex = exec_state(*plan);
         if (ex->launches.empty()) return AR_OK;
+        const bool one = takes_one(*plan, *ex, bufs.data());
         DevState* d = nullptr;
-        ar_status s = device_state(*plan, *ex, &d);
+        ar_status s = device_state(*plan, *ex, one, &d);
         if (s != AR_OK) return s;
         PtrEntry* pe = nullptr;
-        s = step_records(*plan, *ex, *d, bufs, stream, &pe);
+        s = step_records(*plan, *ex, *d, bufs, one, stream, &pe);
         if (s != AR_OK) return s;
-        const DevView v{d->tiles, d->cuts, d->sched_off, d->sched, d->stiles,
-                        d->runits, d->prog, pe->dev, pe->aligned};
+        DevView v{d->tiles, d->cuts, d->sched_off, d->sched, d->stiles,
+                  d->runits, d->prog, pe->dev, pe->aligned};
+        if (one) {
+            v.one = true;
+            v.one_segs = d->one_segs;
+            v.one_prog = d->one_prog;
+            v.one_tiles = d->one_tiles;
+            v.ptrs = pe->dev;
+        }
         return launch_all(plan, ex, v, stream, timer);
     } catch (const std::bad_alloc&) {
         return fail(AR_ERR_OOM, "host allocation failed");
@@ -499,6 +580,7 @@ namespace {
 struct ScratchDev {
     uint8_t* ptr = nullptr;       // device address of `scratch` on this device
     uint64_t serial = 0;          // executor state whose tables it holds
+    bool one = false;             // ... the one-pass launch's
     std::vector<void*> bufs;      // buffer set whose records it holds
 };
 std::mutex g_scratch_mu;
@@ -510,9 +592,29 @@ int64_t img_align(int64_t b) { return (b + kImgAlign - 1) / kImgAlign * kImgAlig
 
 }  // namespace
 
+// Bytes of the image of `ex`: its tables and the records of one buffer set.
+// The limit holds for this size, whichever launches the call runs.
+static int64_t image_bytes(const Plan& p, const ExecState& ex) {
+    size_t cuts = 0, soff = 0, sched = 0, tiles = 0, runits = 0, prog = 0;
+    for (const SliceDesc& sd : ex.slices) {
+        cuts += sd.cuts.size();
+        soff += sd.sched_off.size();
+        sched += sd.sched.size();
+        tiles += sd.tiles.size();
+        runits += sd.runits.size();
+        prog += sd.prog.size();
+    }
+    int64_t at = 0;
+    for (size_t b : {ex.htiles.size() * sizeof(int2), cuts * sizeof(int64_t), soff * sizeof(int32_t),
+                     sched * sizeof(int32_t), tiles * sizeof(int2), runits * sizeof(ResUnit),
+                     prog * sizeof(uint32_t), size_t(ex.rec_words + p.n) * sizeof(uint64_t)})
+        at = img_align(at + int64_t(b));
+    return at;
+}
+
 // Lay out the tables of `ex` and room for the records of one buffer set in
-// ex->img; returns the image's size in bytes.
-static int64_t build_image(const Plan& p, ExecState& ex) {
+// ex->img.
+static void build_image(const Plan& p, ExecState& ex) {
     const SliceTables t = slice_tables(ex);
     const int64_t sizes[8] = {
         int64_t(ex.htiles.size() * sizeof(int2)), int64_t(t.cuts.size() * sizeof(int64_t)),
@@ -525,14 +627,32 @@ static int64_t build_image(const Plan& p, ExecState& ex) {
         ex.img_off[i] = at;
         at = img_align(at + sizes[i]);
     }
-    if (at > int64_t(AR_NOALLOC_MAX_BYTES)) return at;
     ex.img.assign(size_t(at / 8), 0);
     char* b = reinterpret_cast<char*>(ex.img.data());
     const void* src[7] = {ex.htiles.data(), t.cuts.data(), t.soff.data(), t.sched.data(),
                           t.tiles.data(), t.runits.data(), t.prog.data()};
     for (int i = 0; i < 7; ++i)
         if (sizes[i]) std::memcpy(b + ex.img_off[i], src[i], size_t(sizes[i]));
-    return at;
+}
+
+// The same for the one-pass launch: segments, leaves, tiles, then room for
+// the n buffer pointers; empty when it exceeds the array.
+static void build_one_image(const Plan& p, ExecState& ex) {
+    const OnePlan& o = ex.one;
+    const int64_t sizes[4] = {
+        int64_t(o.segs.size() * sizeof(OneSeg)), int64_t(o.prog.size() * sizeof(uint32_t)),
+        int64_t(o.tiles.size() * sizeof(int2)), int64_t(p.n) * int64_t(sizeof(uint64_t))};
+    int64_t at = 0;
+    for (int i = 0; i < 4; ++i) {
+        ex.one_img_off[i] = at;
+        at = img_align(at + sizes[i]);
+    }
+    if (at > int64_t(AR_NOALLOC_MAX_BYTES)) return;
+    ex.one_img.assign(size_t(at / 8), 0);
+    char* b = reinterpret_cast<char*>(ex.one_img.data());
+    const void* src[3] = {o.segs.data(), o.prog.data(), o.tiles.data()};
+    for (int i = 0; i < 3; ++i)
+        if (sizes[i]) std::memcpy(b + ex.one_img_off[i], src[i], size_t(sizes[i]));
 }
 
 AR_EXPORT ar_status ar_plan_execute_noalloc(ar_plan* plan, void* const* bufs, void* stream) {
@@ -546,14 +666,21 @@ AR_EXPORT ar_status ar_plan_execute_noalloc(ar_plan* plan, void* const* bufs, vo
         const std::vector<void*> set(bufs, bufs + plan->n);
         ar_status s = check_buffers(*plan, set);
         if (s != AR_OK) return s;
-        if (ex->img.empty()) {
-            const int64_t need = build_image(*plan, *ex);
-            if (ex->img.empty())
+        bool one = takes_one(*plan, *ex, bufs);
+        if (ex->img.empty() && ex->one_img.empty()) {
+            const int64_t need = image_bytes(*plan, *ex);
+            if (need > int64_t(AR_NOALLOC_MAX_BYTES))
                 return fail(AR_ERR_UNSUPPORTED,
                             "the plan's tables and step records take " + std::to_string(need) +
                                 " bytes; ar_plan_execute_noalloc holds at most " +
                                 std::to_string(int64_t(AR_NOALLOC_MAX_BYTES)));
         }
+        if (one && ex->one_img.empty()) {
+            build_one_image(*plan, *ex);
+            one = !ex->one_img.empty();
+        }
+        if (!one && ex->img.empty()) build_image(*plan, *ex);
+        std::vector<uint64_t>& img = one ? ex->one_img : ex->img;
         int dev = -1;
         hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess) return fail(AR_ERR_HIP, hip_msg("hipGetDevice", e));
@@ -572,20 +699,33 @@ AR_EXPORT ar_status ar_plan_execute_noalloc(ar_plan* plan, void* const* bufs, vo
                 sd.ptr = static_cast<uint8_t*>(ptr);
             }
             base = sd.ptr;
-            const bool tables = sd.serial != ex->serial;
+            const bool tables = sd.serial != ex->serial || sd.one != one;
             if (tables || sd.bufs != set) {
-                const int64_t rec = ex->img_off[7];
-                const int64_t end = int64_t(ex->img.size()) * 8;
-                fill_records(*ex, bufs, plan->n,
-                             ex->img.data() + rec / int64_t(sizeof(uint64_t)));
+                const int64_t rec = one ? ex->one_img_off[3] : ex->img_off[7];
+                const int64_t end = int64_t(img.size()) * 8;
+                uint64_t* const r = img.data() + rec / int64_t(sizeof(uint64_t));
+                if (one) std::memcpy(r, bufs, size_t(plan->n) * sizeof(uint64_t));
+                else fill_records(*ex, bufs, plan->n, r);
                 const int64_t from = tables ? 0 : rec;
                 sd.serial = 0;  // unknown until the copy is enqueued
-                e = hipMemcpyAsync(base + from, reinterpret_cast<const char*>(ex->img.data()) + from,
+                e = hipMemcpyAsync(base + from, reinterpret_cast<const char*>(img.data()) + from,
                                    size_t(end - from), hipMemcpyHostToDevice, st);
                 if (e != hipSuccess) return fail(AR_ERR_HIP, hip_msg("scratch upload", e));
                 sd.serial = ex->serial;
+                sd.one = one;
                 sd.bufs = set;
             }
+        }
+        if (one) {
+            DevView v{};
+            v.aligned = buffers_aligned(bufs, plan->n);
+            v.one = true;
+            v.one_segs = reinterpret_cast<const OneSeg*>(base + ex->one_img_off[0]);
+            v.one_prog = reinterpret_cast<const uint32_t*>(base + ex->one_img_off[1]);
+            if (!ex->one.tiles.empty())
+                v.one_tiles = reinterpret_cast<const int2*>(base + ex->one_img_off[2]);
+            v.ptrs = reinterpret_cast<const uint64_t*>(base + ex->one_img_off[3]);
+            return launch_all(plan, ex, v, st, nullptr);
         }
         auto at = [&](int i) { return base + ex->img_off[i]; };
         const DevView v{reinterpret_cast<const int2*>(at(0)), reinterpret_cast<const int64_t*>(at(1)),
@@ -736,6 +876,8 @@ AR_EXPORT ar_status ar_plan_launch_kernel(const ar_plan* plan, int32_t i, int32_
             const SliceDesc& sd = ex->slices[size_t(stg.slice)];
             *kernel = sd.streamed ? AR_KERNEL_STREAM : sd.resident ? AR_KERNEL_RESIDENT
                                                                    : AR_KERNEL_SLICED;
+        } else if (stg.launch < 0) {
+            *kernel = AR_KERNEL_RESIDENT;
         } else {
             *kernel = ex->launches[size_t(stg.launch)].dsplit > 1 ? AR_KERNEL_SPLIT
                                                                    : AR_KERNEL_PHASE;
@@ -765,6 +907,14 @@ AR_EXPORT ar_status ar_plan_launch_info(const ar_plan* plan, int32_t i, int32_t*
             if (max_dst) *max_dst = sd.max_dst;
             if (num_steps) *num_steps = sd.nsteps;
             if (bytes) *bytes = sd.resident ? sd.res_bytes : sd.bytes;
+            return AR_OK;
+        }
+        if (stg.launch < 0) {  // the one-pass launch
+            if (phase) *phase = -2;
+            if (nsrc) *nsrc = ex->one.max_k;
+            if (max_dst) *max_dst = ex->one.max_dst;
+            if (num_steps) *num_steps = ex->one.nsteps;
+            if (bytes) *bytes = ex->one.bytes;
             return AR_OK;
         }
         const LaunchDesc& L = ex->launches[size_t(stg.launch)];

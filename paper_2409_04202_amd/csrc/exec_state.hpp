@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "kernels.hpp"
+#include "onepass.hpp"
 #include "resident.hpp"
 #include "../../include/ar_plan.h"
 #include "plan.hpp"
@@ -186,6 +187,7 @@ constexpr int64_t kNumXCDs = 8;         // compute dies, each with its own L2
 // (kStreamGain 1): on the 48 plans it was then picked 7 times, each a win.
 constexpr double kStreamWordNs = 145.0;
 constexpr double kStreamGain = 1.0;
+constexpr int32_t kStreamAhead = 48;  // rows a streamed program loads ahead of their use
 // With more than kResMaxN buffers (beyond the plans the model was fitted
 // on) a plain sliced run leaves out phases whose steps store to at least
 // kSplitMinDst buffers over ranges shorter than kSlicedManyDstMinBytes: a
@@ -226,6 +228,49 @@ constexpr int32_t kSplitWideDst = 16;
 // (182 -> 189 us), which read its output from other XCDs.
 constexpr int64_t kAffinityMaxBytes = int64_t(64) << 20;
 constexpr int64_t kAffinityBigBytes = int64_t(512) << 20;
+
+// One-pass form (onepass_kernel).  Limits of what its builder takes on: n,
+// segments, leaf words, and the sources and destinations of the steps summed
+// over the segments they cover (host time and table size).
+constexpr int32_t kOneMaxN = 4096;
+constexpr int64_t kOneMaxSegs = int64_t(1) << 16;
+constexpr int64_t kOneMaxWords = int64_t(1) << 20;
+constexpr int64_t kOneMaxWork = int64_t(1) << 22;
+// Tiles of 64 16-byte vectors up to which lanes take 4 bytes, from which U is
+// 4 and 16, and the wavefronts up to which such a launch is resident at once
+// (one_config).
+constexpr int64_t kOneNarrowTiles = 512;
+constexpr int64_t kOneMinU4 = 3072;
+constexpr int64_t kOneMinU16 = 7168;
+constexpr int64_t kOneMaxResident = 2048;
+// n * N * e from which a one-pass launch loads and stores nontemporally.
+constexpr int64_t kOneNtBytes = int64_t(96) << 20;
+// Its predicted time: kLaunchNs plus the larger of a wavefront's work (kOneLatNs
+// and, for its leaves one after the other, kOneLeafNs each, kOneRoundNs more
+// in a chain of bf16 steps, kOnePushNs per sum put aside) and the bytes, plus
+// kOneOverlap of the smaller.  On MI355X (us): Ring n = 64 over 4K fp32 8.4,
+// n = 128 15.4, RHD n = 64 and 128 12.5 and 23.7 (31 and 63 sums put aside),
+// the (8, 8, 8) tree over 512 buffers 60; over 2^18 (64 MiB in and out) Ring
+// n = 64 20.6, over 2^20 91.
+constexpr double kOneLatNs = 800.0;
+constexpr double kOneLeafNs = 90.0;
+constexpr double kOneRoundNs = 25.0;
+constexpr double kOnePushNs = 130.0;
+constexpr double kOneBytesPerNs = 5700.0;
+constexpr double kOneCachedBytesPerNs = 7200.0;
+constexpr double kOneOverlap = 0.2;
+// On buffers and step boundaries that are all 16-byte aligned it takes the
+// place of several launches when predicted at most kOneGain of their time: the
+// two predictions are off by up to a fifth each (over buffer sets in turn
+// the launches' is low: the (8, 8) tree over 2^20 fp32 139 us, predicted 85).
+// Otherwise no phases can share a launch and each does its steps' ends or, on
+// unaligned buffers, everything element-wise, so it does so always up to
+// kOneFreeN buffers.  Measured on 167 plans with n = 5 to 512 over 1003 to
+// 4194309 elements: 0.03 to 1.05 of the phase launches' time, half of them
+// under 0.45 (the (8, 8) tree over 1048581 fp32 128 -> 98 us, rows of one
+// dense matrix 199 -> 114).  Beyond kOneFreeN it must be predicted faster.
+constexpr double kOneGain = 0.7;
+constexpr int32_t kOneFreeN = 512;
 
 // XCD of a tile starting at element e of N: each XCD owns a contiguous
 // 1/kNumXCDs of every buffer's element range.  Launches with an affinity
@@ -283,7 +328,13 @@ struct DevState {
     int2* stiles = nullptr;
     ResUnit* runits = nullptr;   // resident units and records, all slices concatenated
     uint32_t* prog = nullptr;
+    bool staged = false;         // the tables above are there
+    OneSeg* one_segs = nullptr;  // one-pass launch
+    uint32_t* one_prog = nullptr;
+    int2* one_tiles = nullptr;
+    bool one = false;            // its tables are there
     PtrEntry cache[kCache];
+    PtrEntry one_cache[kCache];  // the n buffer pointers alone
     uint64_t clock = 0;
 };
 
@@ -337,8 +388,30 @@ struct SliceDesc {
     int64_t res_bytes = 0;       // bytes the resident launch loads and stores
 };
 
+// The one-pass form of the whole plan (onepass.cpp): the segments, their
+// leaves, the tiling and the kernel instance.
+enum OneKind { ONE_LB4, ONE_U1B4, ONE_U1B8, ONE_U1B16, ONE_U4, ONE_U16 };
+struct OneConf {
+    int32_t kind;            // OneKind
+    int32_t lb, u, waves;    // bytes of a vector, vectors per lane, waves per workgroup
+};
+struct OnePlan {
+    bool tried = false;      // built, or found to have none
+    bool ok = false;         // every buffer ends with one value at every position
+    bool chain = false;      // a chain of bf16 steps
+    int32_t pushes = 0;      // most sums put aside in a segment
+    OneConf conf{};
+    int32_t depth = 0;       // sums put aside at once
+    int32_t cm = 0;          // cache mode, as LaunchDesc's
+    int32_t max_k = 0, max_dst = 0;
+    int64_t nsteps = 0, bytes = 0, nunits = 0, tiles_per_seg = 0;
+    std::vector<OneSeg> segs;
+    std::vector<uint32_t> prog;
+    std::vector<int2> tiles;  // empty: arithmetic
+};
+
 // One launch of an execution: a sliced launch (slice >= 0) or the phase
-// launch `launch`.
+// launch `launch`, or (both -1) the one-pass launch.
 struct Stage {
     int32_t slice;
     int32_t launch;
@@ -356,6 +429,13 @@ struct ExecState {
                                  // pointers follow them (resident launches)
     std::vector<SliceDesc> slices;
     std::vector<Stage> stages;   // the launches for 16-byte aligned buffers
+    std::vector<Stage> run_stages;  // the same without the one-pass launch
+    OnePlan one;
+    bool one_aligned = false;    // 16-byte aligned buffers run one.  `stages`
+                                 // is then that launch, or the resident or
+                                 // streamed slice whose form it takes
+    bool one_unaligned = false;  // others may (each at its element's alignment),
+                                 // when there is a one-pass form
     std::vector<DevState*> dev;  // indexed by device ordinal
     uint64_t serial = 0;         // unique per executor state ever built
     // ar_plan_execute_noalloc: the tables and step records laid out as in
@@ -363,6 +443,8 @@ struct ExecState {
     std::vector<uint64_t> img;
     int64_t img_off[8] = {};     // byte offsets: tiles, cuts, sched_off,
                                  // sched, stiles, runits, prog, records
+    std::vector<uint64_t> one_img;  // the same for the one-pass launch
+    int64_t one_img_off[4] = {};    // segments, leaves, tiles, buffer pointers
 };
 
 // Every (buffer, range) a phase touches, with the step touching it; answers
@@ -418,5 +500,14 @@ int32_t res_waves(int32_t n, int64_t units);
 // The resident (n <= kResMaxN) or streamed form of sliced run `sd`, in place;
 // `sd` stays plain when its program cannot be built (programs.cpp).
 void build_resident(const Plan& p, const ExecState& ex, SliceDesc& sd);
+// The one-pass form of the plan's executed phases, built on the first call;
+// one.ok stays false when there is none (onepass.cpp).
+void build_onepass(const Plan& p, const ExecState& ex, OnePlan& one);
+OneConf one_config(int32_t n, int64_t tiles16, int32_t depth, int32_t dtype);
+// Its predicted time, ns, and whether its bytes take more of it than a
+// wavefront's work.  Of a form not built yet, a lower bound, and whether they
+// may.
+double onepass_time(const Plan& p, const OnePlan& one);
+bool onepass_streams(const Plan& p, const OnePlan& one);
 
 }  // namespace arp

@@ -127,7 +127,6 @@ static void encode_segment(const std::vector<const XStep*>& st, std::vector<uint
 // into a buffer whose row the segment still has to load waits until the end.
 // Fills w (64-word chunks) and the slots, loads and stores it uses; false when
 // a fold has more than 252 sources or the slots run out.
-constexpr int32_t kStreamAhead = 48;
 // waves of a streamed workgroup (the kernel is written for 1 or 4; one wave
 // owning the whole tile measured the same as four owning a quarter each, and
 // the executor launches four)

@@ -541,6 +541,20 @@ static double stream_time(const Plan& p, const SliceDesc& sd) {
     return kLaunchNs + rounds * double(sd.max_nw) * kStreamWordNs;
 }
 
+// What a whole-plan streamed launch takes at least, for the built-in kinds: a
+// program loads every buffer's row (a word each) and stores every buffer (half
+// a word each), with kStreamAhead rows in LDS where there are so many.  Building the programs
+// only to price them took most of the first call of the (8, 8, 8) tree over
+// 512 buffers (26 ms).
+static double stream_bound(const Plan& p) {
+    if (p.kind < 0) return 0.0;  // a custom plan may touch few buffers
+    const int64_t words = int64_t(p.n) + p.n / 2;
+    const int64_t lds = std::min<int64_t>(p.n, kStreamAhead) * 1024 + int64_t(p.n) * 8 + words * 4;
+    const int64_t per_cu = std::max<int64_t>(1, kLdsBytesPerCU / lds);
+    const int64_t units = (p.N * p.esize + 1023) / 1024;
+    return kLaunchNs + std::ceil(double(units) / double(kNumCUs * per_cu)) * double(words) * kStreamWordNs;
+}
+
 static std::atomic<uint64_t> g_exec_serial{0};
 
 ExecState* exec_state(Plan& p) {
@@ -554,12 +568,32 @@ ExecState* exec_state(Plan& p) {
             const int32_t P = int32_t(ex->phases.size());
             SliceDesc streamed;  // the whole plan streamed, when chosen below
             bool have_streamed = false;
+            // The one-pass form (AR_OPT_RESIDENT), see kOneGain; built only
+            // where its bound says that it may be taken
+            auto one_time = [&]() {
+                build_onepass(p, *ex, ex->one);
+                return ex->one.ok ? onepass_time(p, ex->one)
+                                  : std::numeric_limits<double>::infinity();
+            };
+            bool one_stage = false;
             if (p.slice == 1 && P > 0) {
                 runs.push_back({0, P, p.resident != 0});
             } else if (p.slice == 2) {
                 double t_runs = 0.0;
-                runs = choose_runs(p, *ex, phase_costs(p, *ex), &t_runs);
-                if (p.resident != 0 && p.n > kResMaxN && P > 0) {
+                const std::vector<PhaseCost> pc = phase_costs(p, *ex);
+                runs = choose_runs(p, *ex, pc, &t_runs);
+                double t_phases = 0.0;
+                for (const PhaseCost& c : pc) t_phases += c.t_launch;
+                bool ragged = false;  // a step boundary off 16 bytes
+                for (const PhaseCost& c : pc) ragged = ragged || !c.aligned;
+                const bool one_may = p.resident != 0 && p.n >= 2;
+                ex->one_unaligned =
+                    one_may && (p.n <= kOneFreeN || onepass_time(p, ex->one) < t_phases);
+                if (ragged && ex->one_unaligned)
+                    one_stage = one_time() < (p.n <= kOneFreeN ? std::numeric_limits<double>::infinity()
+                                                               : t_phases);
+                if (p.resident != 0 && p.n > kResMaxN && P > 0 && !ragged &&
+                    stream_bound(p) < kStreamGain * t_runs) {
                     SliceDesc sd = build_slice(p, *ex, 0, P);
                     if (sd.ok) {
                         build_resident(p, *ex, sd);
@@ -567,15 +601,36 @@ ExecState* exec_state(Plan& p) {
                             runs.assign(1, Run{0, P, true});
                             streamed = std::move(sd);
                             have_streamed = true;
+                            t_runs = stream_time(p, streamed);
                         }
                     }
                 }
+                const bool whole = runs.size() == 1 && runs[0].a == 0 && runs[0].b == P;
+                if (one_may && !ragged && !whole && onepass_time(p, ex->one) < kOneGain * t_runs)
+                    one_stage = one_time() < kOneGain * t_runs;
             }
             std::vector<int32_t> slice_of(ex->phases.size(), -1);
             for (const Run& r : runs) {
                 SliceDesc sd = have_streamed ? std::move(streamed) : build_slice(p, *ex, r.a, r.b);
                 if (!sd.ok) continue;  // phase launches for these phases
                 if (r.resident && !have_streamed) build_resident(p, *ex, sd);
+                // A whole-plan launch takes the one-pass form where that is
+                // bound by its bytes: the resident form shares a tile's
+                // leaves among four waves, which is faster where the time is
+                // the leaves' (Ring n = 64 over 2^16 bf16 8.9 us, one-pass
+                // 11.1), and moves each byte once too, but with less in
+                // flight (over 2^18 17.3 us, one-pass 14.1).  A streamed one
+                // runs its records one after the other and takes it where
+                // predicted faster (Ring n = 128 over 2^12 fp32 77 us, 15).
+                if (r.a == 0 && r.b == P && p.resident != 0 && p.n >= 2) {
+                    if (sd.streamed) {
+                        const double t = stream_time(p, sd);
+                        ex->one_aligned = onepass_time(p, ex->one) < t && one_time() < t;
+                    } else {
+                        ex->one_aligned = onepass_streams(p, ex->one) && one_time() >= 0.0 &&
+                                          ex->one.ok && onepass_streams(p, ex->one);
+                    }
+                }
                 sd.cuts_base = ex->slices.empty() ? 0
                                                   : ex->slices.back().cuts_base +
                                                         int64_t(ex->slices.back().cuts.size());
@@ -602,11 +657,16 @@ ExecState* exec_state(Plan& p) {
             for (size_t li = 0; li < ex->launches.size(); ++li) {
                 const int32_t sl = slice_of[size_t(ex->launches[li].xphase)];
                 if (sl < 0) {
-                    ex->stages.push_back({-1, int32_t(li)});
+                    ex->run_stages.push_back({-1, int32_t(li)});
                 } else if (sl != last) {
-                    ex->stages.push_back({sl, -1});
+                    ex->run_stages.push_back({sl, -1});
                     last = sl;
                 }
+            }
+            ex->stages = ex->run_stages;
+            if (one_stage) {
+                ex->stages.assign(1, Stage{-1, -1});
+                ex->one_aligned = true;
             }
         } catch (...) {
             delete ex;

@@ -1,0 +1,151 @@
+"""The one-pass launch (csrc/onepass.hpp): a whole AllReduce as one launch with
+its values in registers, the form that plans whose steps do not lie on 16-byte
+boundaries and buffers that do not take by default.
+
+On the host, the library's check runs every segment's leaves on terms against
+the executed steps and walks the tiles of every kernel instance.  On the GPU,
+results equal the oracle's bit for bit at the sizes where the tiling changes.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2409_04202_amd import workloads
+
+from checklib import arplan as check
+from test_capi_host import _check_tiling
+
+if torch.cuda.is_available():
+    from gpu_helpers import run_plan, say, to_device, to_host
+    from paper_2409_04202_amd import arplan
+
+ASY = workloads.preorder([[4, 4], [4, 2], 3, [2]])  # uneven switches, 19 servers
+
+PLANS = [("ring", 2, None), ("ring", 5, None), ("ring", 64, None), ("ring", 70, None),
+         ("rhd", 8, None), ("rhd", 12, None), ("rhd", 96, None), ("cps", 3, None),
+         ("cps", 70, None), ("rb", 6, None), ("tree", 12, (3, 4)), ("tree", 24, (2, 3, 4)),
+         ("tree", 96, (8, 12)), ("gentree", 19, tuple(ASY))]
+
+
+@pytest.mark.parametrize("kind,n,fan", PLANS)
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "i32"])
+def test_program_and_tiles(kind, n, fan, dtype):
+    # N off the processors and the vectors; around a tile of 64 4-byte lanes;
+    # where the instance changes (512, 3072 and 7168 tiles of 1 KiB)
+    es = 2 if dtype == "bf16" else 4
+    kib = 1024 // es
+    for N in (16 // es + 1, 67, max(n + 1, 16 // es), 64 * 4 // es + 1, 5 * n + 3, 513 * kib - 1, 3072 * kib + 3,
+              7168 * kib + 5):
+        with check.Plan(n, N, dtype, kind, fan) as p:
+            L = p.launches()
+            if n <= 512 and N % n:
+                # a step boundary off 16 bytes: one launch moving each byte once
+                assert [x[0] for x in L] == [-2] and L[0][4] == 2 * n * N * es, (N, L)
+                assert p.launch_kernels() == ["resident_kernel"]
+            for fuse in (1, 0):
+                p.set_option(check.AR_OPT_FUSE, fuse)
+                for vecok in (1, 0):
+                    st, msg = _check_tiling(p.handle, vecok)
+                    assert st == check.AR_OK, (N, msg)
+            # not without resident launches, nor without sliced ones
+            p.set_option(check.AR_OPT_RESIDENT, 0)
+            assert all(x[0] >= -1 for x in p.launches())
+
+
+def test_plans_that_have_no_one_pass_form():
+    # buffers that end with different values, positions no step covers, a
+    # plain copy (its bits are not to pass through an addition)
+    N = 1001
+    for n, steps in ((3, [(0, "reduce", 0, [0, 1], 0, N), (0, "copy", 2, [1], 0, N)]),
+                     (2, [(0, "reduce", 0, [0, 1], 0, 500), (1, "copy", 1, [0], 0, 500)]),
+                     (2, [(0, "copy", 1, [0], 0, N)])):
+        h = check.ar_plan_create_custom(n, N, "f32", steps)
+        try:
+            L = [check.ar_plan_launch_info(h, i) for i in range(check.ar_plan_num_launches(h))]
+            assert all(x[0] >= 0 for x in L), L
+            for vecok in (1, 0):
+                st, msg = _check_tiling(h, vecok)
+                assert st == check.AR_OK, msg
+        finally:
+            check.ar_plan_destroy(h)
+
+
+# (kind, n, N, dtype, fan): every instance, with a partial last vector
+GPU = [("ring", 5, 67, "f32", None), ("rhd", 5, 4099, "f32", None), ("rhd", 7, 4099, "bf16", None),
+       ("tree", 15, 4099, "f32", (3, 5)), ("tree", 35, 4099, "bf16", (5, 7)), ("ring", 64, 8195, "bf16", None), ("rhd", 12, 4099, "bf16", None),
+       ("tree", 24, 20011, "i32", (2, 3, 4)), ("cps", 70, 1003, "bf16", None),
+       ("gentree", 19, 30011, "bf16", tuple(ASY)), ("rhd", 96, 5003, "f32", None),
+       ("cps", 3, 513 * 256 + 1, "f32", None), ("rhd", 6, 513 * 512 + 3, "bf16", None),
+       ("tree", 12, 600 * 256 + 7, "f32", (3, 4)), ("ring", 17, 600 * 512 + 9, "bf16", None),
+       ("rhd", 4, 3072 * 256 + 5, "f32", None), ("tree", 6, 3072 * 512 + 5, "bf16", (3, 2)),
+       ("cps", 3, 7168 * 256 + 3, "i32", None), ("rhd", 4, 7168 * 512 + 7, "bf16", None),
+       ("rhd", 4, 7168 * 1024 + 3, "f32", None), ("cps", 2, 2049 * 16 * 512 + 5, "bf16", None)]
+
+
+def _oracle_plan(kind, n, N, fan):
+    if kind == "gentree":
+        return oracle.gentree_plan(oracle.from_preorder(fan), N)
+    return oracle.make_plan(kind, n, N, fan)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,n,N,dtype,fan", GPU)
+def test_bit_exact(kind, n, N, dtype, fan):
+    dist = "int1000" if dtype == "i32" else "uniform"
+    xs0 = workloads.draw(n, N, dtype, dist, N % 89)
+    want = oracle.execute(_oracle_plan(kind, n, N, fan), [x.copy() for x in xs0], dtype)
+    # aligned buffers, and buffers each a few elements off 16 bytes
+    for pad in (0, 1, 3):
+        say("case: one-pass %s n=%d N=%d %s pad=%d" % (kind, n, N, dtype, pad))
+        ts = to_device(xs0, dtype, pad)
+        with arplan.Plan(n, N, dtype, kind, fan) as p:
+            run_plan(p, ts)
+        got = to_host(ts, dtype)
+        for q in range(n):
+            assert np.array_equal(got[q], want[q]), (pad, q)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "i32"])
+def test_dense_rows_leave_their_surroundings_alone(dtype):
+    # rows of one matrix of odd width (each row at another alignment), with
+    # guard elements around it, through the strided and the no-allocation
+    # entry points; special values among the inputs
+    n, N = 9, 4101
+    t = {"f32": torch.float32, "i32": torch.int32, "bf16": torch.bfloat16}[dtype]
+    rng = np.random.default_rng(5)
+    x = rng.integers(-100, 101, size=(n, N)).astype(np.float32)
+    if dtype != "i32":
+        x[rng.integers(0, n, 300), rng.integers(0, N, 300)] = np.inf
+        x[rng.integers(0, n, 300), rng.integers(0, N, 300)] = -0.0
+        x[:, :50] = -0.0
+        x[:, 50:90] *= 1e-40  # denormal
+        x[0, 100:120] = np.nan
+    for kind in ("ring", "cps", "tree"):
+        for entry in ("strided", "noalloc"):
+            say("case: one-pass dense %s %s %s" % (kind, entry, dtype))
+            outs = []
+            for res in (1, 0):  # against the phase launches
+                g = torch.full((n * N + 64,), 7, dtype=t, device="cuda")
+                m = g[33:33 + n * N].view(n, N)
+                m.copy_(torch.from_numpy(x).to(t))
+                with arplan.Plan(n, N, dtype, kind, (3, 3) if kind == "tree" else None) as p:
+                    p.set_option(arplan.AR_OPT_RESIDENT, res)
+                    s = torch.cuda.current_stream()
+                    if entry == "strided":
+                        p.execute_strided(m, N * m.element_size(), s)
+                    else:
+                        p.execute_noalloc(list(m), s)
+                    torch.cuda.synchronize()
+                assert bool((g[:33] == 7).all()) and bool((g[33 + n * N:] == 7).all())
+                outs.append(m.cpu())
+            a, b = outs
+            if dtype == "i32":
+                assert torch.equal(a, b)
+            else:
+                nan = torch.isnan(b)
+                assert torch.equal(torch.isnan(a), nan)
+                bits = torch.int32 if dtype == "f32" else torch.int16
+                assert torch.equal(a.view(bits)[~nan], b.view(bits)[~nan])
