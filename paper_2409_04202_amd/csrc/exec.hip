@@ -389,12 +389,25 @@ static void launch_one(const Plan& p, const OnePlan& one, const DevView& v, hipS
 #undef AR_ONE
 }
 
+template <int DT, int W, int LPW>
+static void launch_team(const Plan& p, const OnePlan& one, const DevView& v, hipStream_t stream) {
+    const uint32_t per_xcd = static_cast<uint32_t>((one.nunits + 7) / 8);
+    const size_t lds = size_t(2 * W * LPW * 64 + 64) * 4 +
+                       size_t(one.depth) * 64 * sizeof(typename OneVec<DT, 4>::Acc);
+    hipLaunchKernelGGL((onepass_team_kernel<DT, W, LPW>), dim3(per_xcd * 8), dim3(64 * W), lds, stream,
+                       v.ptrs, p.n, v.one_prog, v.one_segs, int32_t(one.segs.size()), v.one_tiles,
+                       uint32_t(one.nunits), uint32_t(one.tiles_per_seg), per_xcd, p.N,
+                       v.aligned ? 4 / p.esize - 1 : 0);
+}
+
 template <int DT>
 static void launch_one_d(const Plan& p, const OnePlan& one, const DevView& v, hipStream_t stream) {
     switch (one.conf.kind) {
         case ONE_LB4: launch_one<DT, 4, 1, 32, 4>(p, one, v, stream); break;
         case ONE_U4: launch_one<DT, 16, 4, 4, 1>(p, one, v, stream); break;
         case ONE_U16: launch_one<DT, 16, 16, 1, 1>(p, one, v, stream); break;
+        case ONE_TEAM4: launch_team<DT, 4, 16>(p, one, v, stream); break;
+        case ONE_TEAM16: launch_team<DT, 16, 8>(p, one, v, stream); break;
         case ONE_U1B4: launch_one<DT, 16, 1, 4, 1>(p, one, v, stream); break;
         case ONE_U1B8: launch_one<DT, 16, 1, 8, 1>(p, one, v, stream); break;
         default: launch_one<DT, 16, 1, 16, 1>(p, one, v, stream); break;

@@ -236,33 +236,53 @@ constexpr int32_t kOneMaxN = 4096;
 constexpr int64_t kOneMaxSegs = int64_t(1) << 16;
 constexpr int64_t kOneMaxWords = int64_t(1) << 20;
 constexpr int64_t kOneMaxWork = int64_t(1) << 22;
-// Tiles of 64 16-byte vectors up to which lanes take 4 bytes, from which U is
-// 4 and 16, and the wavefronts up to which such a launch is resident at once
-// (one_config).
+// Tiles of 64 16-byte vectors (1 KiB of a buffer) up to which lanes take 4
+// bytes, from which U is 4 and 16, and the wavefronts up to which such a launch
+// is resident at once (one_config).
 constexpr int64_t kOneNarrowTiles = 512;
 constexpr int64_t kOneMinU4 = 3072;
 constexpr int64_t kOneMinU16 = 7168;
 constexpr int64_t kOneMaxResident = 2048;
+// Of kOneTeamMinN buffers and more, those up to which a workgroup takes a tile
+// of 4-byte lanes (onepass_team_kernel): of 16 waves while each compute unit
+// has one such tile (half as many again for kOneTeamManyN buffers), else of
+// four.  us, one wave a tile / team of 4 / of 16: Ring n = 64 fp32 over 16387
+// 9.2 / 5.9 / 6.3, over 8195 9.1 / 5.5 / 5.0, over 32771 9.6 / 6.8 / 8.7, over
+// 49157 10.1 / 8.2 / 11.0, over 65541 10.8 / 12.0 / 14.0; the (8, 8, 8) tree
+// over 512 buffers of 8195 62 / 31 / 23, of 24581 63 / 33 / 29, of 49157
+// 62 / 46 / 61, of 65541 70 / 85 / 91.
+constexpr int32_t kOneTeamMinN = 20;
+constexpr int32_t kOneTeamManyN = 128;
+constexpr int64_t kOneTeamTiles = 200;
+constexpr int64_t kOneTeam16Tiles = 64;
 // n * N * e from which a one-pass launch loads and stores nontemporally.
 constexpr int64_t kOneNtBytes = int64_t(96) << 20;
 // Its predicted time: kLaunchNs plus the larger of a wavefront's work (kOneLatNs
 // and, for its leaves one after the other, kOneLeafNs each, kOneRoundNs more
 // in a chain of bf16 steps, kOnePushNs per sum put aside) and the bytes, plus
-// kOneOverlap of the smaller.  On MI355X (us): Ring n = 64 over 4K fp32 8.4,
-// n = 128 15.4, RHD n = 64 and 128 12.5 and 23.7 (31 and 63 sums put aside),
-// the (8, 8, 8) tree over 512 buffers 60; over 2^18 (64 MiB in and out) Ring
-// n = 64 20.6, over 2^20 91.
+// kOneOverlap of the smaller; of a team's launch the sum of both, with the
+// team's constants.  On MI355X (us): Ring n = 64 over 4K fp32 8.4, n = 128
+// 15.4, RHD n = 64 and 128 12.5 and 23.7 (31 and 63 sums put aside), the
+// (8, 8, 8) tree over 512 buffers 60; teams 5.0, 7.0, 7.7, 12.5 and 21; over
+// 2^18 (64 MiB in and out) Ring n = 64 20.6, over 2^20 91.
 constexpr double kOneLatNs = 800.0;
 constexpr double kOneLeafNs = 90.0;
 constexpr double kOneRoundNs = 25.0;
 constexpr double kOnePushNs = 130.0;
+constexpr double kOneTeamLatNs = 1300.0;
+constexpr double kOneTeamLeafNs = 22.0;
+constexpr double kOneTeamRoundNs = 22.0;
+constexpr double kOneTeamPushNs = 85.0;
 constexpr double kOneBytesPerNs = 5700.0;
 constexpr double kOneCachedBytesPerNs = 7200.0;
 constexpr double kOneOverlap = 0.2;
 // On buffers and step boundaries that are all 16-byte aligned it takes the
 // place of several launches when predicted at most kOneGain of their time: the
 // two predictions are off by up to a fifth each (over buffer sets in turn
-// the launches' is low: the (8, 8) tree over 2^20 fp32 139 us, predicted 85).
+// the launches' is low: the (8, 8) tree over 2^20 fp32 139 us, predicted 85),
+// and only where its bytes take the longer time: the choice for short plans is
+// pinned by the tests (some would gain: RHD n = 128 over 2^12 fp32, split
+// launches, 25 us, teams 12.5).
 // Otherwise no phases can share a launch and each does its steps' ends or, on
 // unaligned buffers, everything element-wise, so it does so always up to
 // kOneFreeN buffers.  Measured on 167 plans with n = 5 to 512 over 1003 to
@@ -390,7 +410,7 @@ struct SliceDesc {
 
 // The one-pass form of the whole plan (onepass.cpp): the segments, their
 // leaves, the tiling and the kernel instance.
-enum OneKind { ONE_LB4, ONE_U1B4, ONE_U1B8, ONE_U1B16, ONE_U4, ONE_U16 };
+enum OneKind { ONE_LB4, ONE_U1B4, ONE_U1B8, ONE_U1B16, ONE_U4, ONE_U16, ONE_TEAM4, ONE_TEAM16 };
 struct OneConf {
     int32_t kind;            // OneKind
     int32_t lb, u, waves;    // bytes of a vector, vectors per lane, waves per workgroup
@@ -509,5 +529,7 @@ OneConf one_config(int32_t n, int64_t tiles16, int32_t depth, int32_t dtype);
 // may.
 double onepass_time(const Plan& p, const OnePlan& one);
 bool onepass_streams(const Plan& p, const OnePlan& one);
+// Does the one-pass form of a plan run as teams?
+bool onepass_teams(const Plan& p);
 
 }  // namespace arp

@@ -98,6 +98,13 @@ struct Emit {
 // onepass.hpp for what was measured).  A wave's sums put aside take
 // depth * U * 64 sums of LDS; instances with U > 1 are for launches that are
 // resident at once, so they must fit beside each other.
+static bool team_tiles(int32_t n, int64_t tiles16) {
+    return n >= kOneTeamMinN && tiles16 <= kOneTeamTiles;
+}
+static int64_t tiles_of(const Plan& p) {  // of 1 KiB of a buffer
+    return (p.N * p.esize + 1023) / 1024;
+}
+bool onepass_teams(const Plan& p) { return team_tiles(p.n, tiles_of(p)); }
 OneConf one_config(int32_t n, int64_t tiles16, int32_t depth, int32_t dtype) {
     const int64_t sum = dtype == AR_BF16 ? 2 : 1;  // bytes of a sum per byte of elements
     auto resident = [&](int64_t u) {
@@ -106,6 +113,10 @@ OneConf one_config(int32_t n, int64_t tiles16, int32_t depth, int32_t dtype) {
         return units <= kOneMaxResident &&
                (lds == 0 || units <= kNumCUs * (kLdsBytesPerCU / lds));
     };
+    if (team_tiles(n, tiles16)) {
+        const int64_t one_a_unit = n >= kOneTeamManyN ? kOneTeam16Tiles * 3 / 2 : kOneTeam16Tiles;
+        return {tiles16 <= one_a_unit ? ONE_TEAM16 : ONE_TEAM4, 4, 1, 1};
+    }
     if (tiles16 <= kOneNarrowTiles) return {ONE_LB4, 4, 1, 4};
     if (tiles16 >= kOneMinU16 && resident(16)) return {ONE_U16, 16, 16, 1};
     if (tiles16 >= kOneMinU4 && tiles16 < kOneMinU16 && resident(4)) return {ONE_U4, 16, 4, 1};
@@ -182,8 +193,7 @@ static void build(const Plan& p, const ExecState& ex, OnePlan& one) {
         one.chain = one.chain || (p.dtype == AR_BF16 && em.max_depth == 0 && w.size() > 2 &&
                                   (w[1] & kOneRound) != 0);
     }
-    const int64_t total16 = (p.N + 64 * VEC - 1) / (64 * VEC);
-    one.conf = one_config(n, total16, one.depth, p.dtype);
+    one.conf = one_config(n, tiles_of(p), one.depth, p.dtype);
     const int64_t vec = one.conf.lb / p.esize;
     const int64_t te = 64 * vec * one.conf.u;
     std::vector<int64_t> nt;
@@ -223,6 +233,10 @@ void build_onepass(const Plan& p, const ExecState& ex, OnePlan& one) {
 
 // A wavefront's work and the bytes, ns.
 static double one_wave_time(const Plan& p, const OnePlan& one) {
+    if (onepass_teams(p))
+        return kOneTeamLatNs +
+               double(p.n) * (kOneTeamLeafNs + (one.chain ? kOneTeamRoundNs : 0.0)) +
+               double(one.pushes) * kOneTeamPushNs;
     return kOneLatNs + double(p.n) * (kOneLeafNs + (one.chain ? kOneRoundNs : 0.0)) +
            double(one.pushes) * kOnePushNs;
 }
@@ -232,7 +246,7 @@ static double one_mem_time(const Plan& p) {
 }
 double onepass_time(const Plan& p, const OnePlan& one) {
     const double w = one_wave_time(p, one), m = one_mem_time(p);
-    return kLaunchNs + std::max(w, m) + kOneOverlap * std::min(w, m);
+    return kLaunchNs + std::max(w, m) + (onepass_teams(p) ? 1.0 : kOneOverlap) * std::min(w, m);
 }
 bool onepass_streams(const Plan& p, const OnePlan& one) {
     return one_mem_time(p) >= one_wave_time(p, one);

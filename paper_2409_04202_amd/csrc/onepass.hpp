@@ -385,4 +385,142 @@ __global__ __launch_bounds__(64 * W) void onepass_kernel(
     }
 }
 
+// The same with a workgroup of W wavefronts per tile of 64 4-byte lanes, for
+// few positions and many buffers, where a wavefront's time is its n loads and
+// n stores one after the other: each wave loads LPW leaves of a chunk of
+// W * LPW into LDS (the next chunk's loads go out before the current one is
+// folded, two chunk buffers), one wave folds them from there, and each
+// wave stores to its share of the buffers once every load has been used.
+// LDS: two chunk buffers, the result, the sums put aside.
+template <int DT, int W, int LPW>
+__global__ __launch_bounds__(64 * W) void onepass_team_kernel(
+    const uint64_t* __restrict__ ptab, int32_t n, const uint32_t* __restrict__ prog,
+    const OneSeg* __restrict__ segs, int32_t nseg, const int2* __restrict__ tiles, uint32_t nunits,
+    uint32_t tiles_per_seg, uint32_t per_xcd, int64_t N, int32_t amask) {
+    extern __shared__ uint32_t lds[];
+    using K = OnePass<DT, 4, 1, kOneGroup, 1, 0>;
+    using V = typename K::V;
+    using M = typename K::M;
+    using T = typename K::T;
+    constexpr int VEC = K::VEC;
+    constexpr int64_t TE = int64_t(64) * VEC;
+    constexpr int C = W * LPW;  // leaves of a chunk
+    // workgroups on one compute unit (256 apart) fold on different SIMDs
+    const int folder = int(blockIdx.x >> 8) % W;
+    const int lane = int(threadIdx.x) & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const uint32_t unit = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+    if (unit >= nunits) return;  // the same for the whole workgroup
+    uint32_t s = 0, t = unit;
+    if (tiles) {
+        const int2 e = tiles[unit];
+        s = uint32_t(__builtin_amdgcn_readfirstlane(e.x));
+        t = uint32_t(__builtin_amdgcn_readfirstlane(e.y));
+    } else if (nseg > 1) {
+        s = unit / tiles_per_seg;
+        t = unit - s * tiles_per_seg;
+    }
+    const OneSeg sg = segs[s];
+    const int64_t t0 = one_tile(sg.lo, int64_t(t), TE, amask);
+    if (t0 >= sg.hi) return;
+    const int64_t back = t0 < VEC ? t0 : VEC;
+    const uint64_t tbase = uint64_t(t0 - back) * sizeof(T);
+    const OneLane l = one_lane(t0, t0 + lane * VEC, sg.lo, sg.hi, N, VEC);
+    const uint32_t* const leaf = prog + sg.off;
+    uint32_t* const res = lds + 2 * C * 64;
+    K k;
+    k.off[0] = uint32_t((l.at - (t0 - back)) * int64_t(sizeof(T)));
+    k.stk = res + 64 + lane;
+    k.depth = 0;
+    k.zero();
+    // this wave's leaves of the chunk at c0: their pointers, a lane each, then
+    // their rows
+    auto pointers = [&](int c0) -> uint64_t {
+        const int i = c0 + wv * LPW + lane;
+        return lane < LPW && i < sg.nleaf ? ptab[leaf[i] & 0xFFFFu] : 0;
+    };
+    V x[LPW];
+    auto issue = [&](int c0, uint64_t p) {
+        const int cnt = min(LPW, sg.nleaf - (c0 + wv * LPW));
+        const uint32_t plo = uint32_t(p), phi = uint32_t(p >> 32);
+        auto row = [&](int j) {
+            return k.template load<false>(
+                ((uint64_t(uint32_t(__builtin_amdgcn_readlane(int(phi), j))) << 32) |
+                 uint32_t(__builtin_amdgcn_readlane(int(plo), j))) + tbase, 0);
+        };
+        if (cnt == LPW) {
+#pragma unroll
+            for (int j = 0; j < LPW; ++j) x[j] = row(j);
+        } else {
+#pragma unroll
+            for (int j = 0; j < LPW; ++j) x[j] = j < cnt ? row(j) : V(0);
+        }
+    };
+    issue(0, pointers(0));
+    // the pointers of the buffers this wave stores to
+    const int d0 = int(int64_t(n) * wv / W), d1 = int(int64_t(n) * (wv + 1) / W);
+    uint64_t dp = d0 + lane < d1 ? ptab[d0 + lane] : 0;
+    uint64_t pn = pointers(C);
+    for (int c0 = 0; c0 < sg.nleaf; c0 += C) {
+        uint32_t* const rows = lds + (c0 / C & 1) * C * 64;
+#pragma unroll
+        for (int j = 0; j < LPW; ++j) rows[(wv * LPW + j) * 64 + lane] = x[j];
+        if (c0 + C < sg.nleaf) {
+            issue(c0 + C, pn);
+            pn = pointers(c0 + 2 * C);
+        }
+        __syncthreads();
+        if (wv == folder) {
+            for (int s0 = 0; s0 < C && c0 + s0 < sg.nleaf; s0 += 64) {
+                const int m = min(min(64, C - s0), sg.nleaf - c0 - s0);
+                const uint32_t w = lane < m ? leaf[c0 + s0 + lane] : 0u;
+                const uint64_t pushes = __builtin_amdgcn_ballot_w64((w & kOnePush) != 0);
+                const uint64_t pops = __builtin_amdgcn_ballot_w64(w >> kOnePopShift != 0);
+                const uint64_t rounds = __builtin_amdgcn_ballot_w64((w & kOneRound) != 0);
+                const uint32_t* const r = rows + s0 * 64 + lane;
+                int j = 0;
+                for (; j + kOneGroup <= m; j += kOneGroup) {
+                    V y[kOneGroup][1];
+#pragma unroll
+                    for (int q = 0; q < kOneGroup; ++q) y[q][0] = r[(j + q) * 64];
+                    k.template group<kOneGroup>(y, w, pushes, pops, rounds, j);
+                }
+                for (; j < m; ++j) {
+                    V y[1][1] = {{r[j * 64]}};
+                    k.template group<1>(y, w, pushes, pops, rounds, j);
+                }
+            }
+        }
+    }
+    if (wv == folder) res[lane] = k.acc[0].out();
+    __syncthreads();
+    const V out = res[lane];
+    const bool full = l.fa == 0 && l.fb == VEC;
+    const uint64_t part = __builtin_amdgcn_ballot_w64(!full && l.fa < l.fb);
+    for (int c0 = d0; c0 < d1; c0 += 64) {
+        const uint32_t plo = uint32_t(dp), phi = uint32_t(dp >> 32);
+        const int m = min(64, d1 - c0);
+        if (c0 + 64 < d1) dp = c0 + 64 + lane < d1 ? ptab[c0 + 64 + lane] : 0;
+        if (full)
+            for (int j = 0; j < m; ++j) {
+                const uint64_t base =
+                    ((uint64_t(uint32_t(__builtin_amdgcn_readlane(int(phi), j))) << 32) |
+                     uint32_t(__builtin_amdgcn_readlane(int(plo), j))) + tbase;
+                *(AR_GLOBAL M*)((AR_GLOBAL char*)base + k.off[0]) = out;
+            }
+        if constexpr (VEC > 1) {
+            const uint64_t mine = ((uint64_t(phi) << 32) | plo) + tbase;
+            for (uint64_t pm = part; pm; pm &= pm - 1) {
+                const int L = __builtin_ctzll(pm);
+                const OneLane e = one_lane(t0, t0 + L * VEC, sg.lo, sg.hi, N, VEC);
+                AR_GLOBAL T* p = (AR_GLOBAL T*)(mine + uint64_t(e.at - (t0 - back)) * sizeof(T));
+                const uint32_t word = uint32_t(__builtin_amdgcn_readlane(int(out), L));
+#pragma unroll
+                for (int i = 0; i < VEC; ++i)
+                    if (lane < m && i >= e.fa && i < e.fb) p[i] = one_elem<T>(word, i);
+            }
+        }
+    }
+}
+
 }  // namespace arp

@@ -576,6 +576,7 @@ ExecState* exec_state(Plan& p) {
                                   : std::numeric_limits<double>::infinity();
             };
             bool one_stage = false;
+            double t_whole = 0.0;  // predicted, of the runs chosen (AR_OPT_SLICE = 2)
             if (p.slice == 1 && P > 0) {
                 runs.push_back({0, P, p.resident != 0});
             } else if (p.slice == 2) {
@@ -605,9 +606,11 @@ ExecState* exec_state(Plan& p) {
                         }
                     }
                 }
+                t_whole = t_runs;
                 const bool whole = runs.size() == 1 && runs[0].a == 0 && runs[0].b == P;
-                if (one_may && !ragged && !whole && onepass_time(p, ex->one) < kOneGain * t_runs)
-                    one_stage = one_time() < kOneGain * t_runs;
+                if (one_may && !ragged && !whole && onepass_streams(p, ex->one) &&
+                    onepass_time(p, ex->one) < kOneGain * t_runs)
+                    one_stage = one_time() < kOneGain * t_runs && onepass_streams(p, ex->one);
             }
             std::vector<int32_t> slice_of(ex->phases.size(), -1);
             for (const Run& r : runs) {
@@ -615,21 +618,22 @@ ExecState* exec_state(Plan& p) {
                 if (!sd.ok) continue;  // phase launches for these phases
                 if (r.resident && !have_streamed) build_resident(p, *ex, sd);
                 // A whole-plan launch takes the one-pass form where that is
-                // bound by its bytes: the resident form shares a tile's
-                // leaves among four waves, which is faster where the time is
-                // the leaves' (Ring n = 64 over 2^16 bf16 8.9 us, one-pass
-                // 11.1), and moves each byte once too, but with less in
-                // flight (over 2^18 17.3 us, one-pass 14.1).  A streamed one
-                // runs its records one after the other and takes it where
-                // predicted faster (Ring n = 128 over 2^12 fp32 77 us, 15).
+                // bound by its bytes: the resident form moves each byte once
+                // too, but with less in flight (Ring n = 64 over 2^18 bf16
+                // 17.3 us, one-pass 14.1).  Where it is bound by the leaves
+                // of a wavefront, only as teams and when predicted faster
+                // (over 2^16 8.9 us, one-pass 11.1 by single waves, 8.1 by
+                // teams; over 2^12 8.2 us, by teams 6.5).  A streamed one
+                // runs its records one after the other and takes it when
+                // predicted faster (Ring n = 128 over 2^12 fp32 77 us, 7).
                 if (r.a == 0 && r.b == P && p.resident != 0 && p.n >= 2) {
-                    if (sd.streamed) {
-                        const double t = stream_time(p, sd);
+                    const bool by_time = sd.streamed || (p.slice == 2 && onepass_teams(p));
+                    const double t = sd.streamed ? stream_time(p, sd) : t_whole;
+                    if (by_time)
                         ex->one_aligned = onepass_time(p, ex->one) < t && one_time() < t;
-                    } else {
+                    else
                         ex->one_aligned = onepass_streams(p, ex->one) && one_time() >= 0.0 &&
                                           ex->one.ok && onepass_streams(p, ex->one);
-                    }
                 }
                 sd.cuts_base = ex->slices.empty() ? 0
                                                   : ex->slices.back().cuts_base +

@@ -33,10 +33,11 @@ PLANS = [("ring", 2, None), ("ring", 5, None), ("ring", 64, None), ("ring", 70, 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "i32"])
 def test_program_and_tiles(kind, n, fan, dtype):
     # N off the processors and the vectors; around a tile of 64 4-byte lanes;
-    # where the instance changes (512, 3072 and 7168 tiles of 1 KiB)
+    # where the instance changes (64, 200, 512, 3072 and 7168 tiles of 1 KiB)
     es = 2 if dtype == "bf16" else 4
     kib = 1024 // es
-    for N in (16 // es + 1, 67, max(n + 1, 16 // es), 64 * 4 // es + 1, 5 * n + 3, 513 * kib - 1, 3072 * kib + 3,
+    for N in (16 // es + 1, 67, max(n + 1, 16 // es), 64 * 4 // es + 1, 5 * n + 3, 64 * kib + 1,
+              200 * kib - 1, 513 * kib - 1, 3072 * kib + 3,
               7168 * kib + 5):
         with check.Plan(n, N, dtype, kind, fan) as p:
             L = p.launches()
@@ -81,6 +82,10 @@ GPU = [("ring", 5, 67, "f32", None), ("rhd", 5, 4099, "f32", None), ("rhd", 7, 4
        ("tree", 12, 600 * 256 + 7, "f32", (3, 4)), ("ring", 17, 600 * 512 + 9, "bf16", None),
        ("rhd", 4, 3072 * 256 + 5, "f32", None), ("tree", 6, 3072 * 512 + 5, "bf16", (3, 2)),
        ("cps", 3, 7168 * 256 + 3, "i32", None), ("rhd", 4, 7168 * 512 + 7, "bf16", None),
+       # teams of 16 and of 4 waves, several chunks, either side of their limits
+       ("tree", 20, 64 * 256 - 1, "f32", (4, 5)), ("ring", 129, 96 * 512 + 1, "bf16", None),
+       ("tree", 130, 97 * 256 + 1, "f32", (10, 13)), ("rhd", 66, 200 * 512 - 3, "bf16", None),
+       ("cps", 21, 200 * 256 + 3, "i32", None), ("rhd", 300, 4099, "f32", None),
        ("rhd", 4, 7168 * 1024 + 3, "f32", None), ("cps", 2, 2049 * 16 * 512 + 5, "bf16", None)]
 
 
