@@ -376,9 +376,11 @@ struct DevView {
 template <int DT, int LB, int U, int B, int W>
 static void launch_one(const Plan& p, const OnePlan& one, const DevView& v, hipStream_t stream) {
     const int64_t blocks = (one.nunits + W - 1) / W;
-    const uint32_t per_xcd = static_cast<uint32_t>((blocks + 7) / 8);
-    const dim3 grid(per_xcd * 8), block(64 * W);
-    const size_t lds = size_t(one.depth) * U * 64 * W * sizeof(typename OneVec<DT, LB>::Acc);
+    const bool many = U == 1 && W == 1 && one.many;
+    const uint32_t per_xcd = many ? 0u : static_cast<uint32_t>((blocks + 7) / 8);
+    const dim3 grid(many ? static_cast<uint32_t>(blocks) : per_xcd * 8), block(64 * W);
+    const size_t lds = std::max(size_t(one.depth) * U * 64 * W * sizeof(typename OneVec<DT, LB>::Acc),
+                                many ? size_t(one_lds(p.n)) : size_t(0));
     const int32_t amask = v.aligned ? LB / p.esize - 1 : 0;
 #define AR_ONE(CM)                                                                            \
     hipLaunchKernelGGL((onepass_kernel<DT, LB, U, B, W, CM>), grid, block, lds, stream, v.ptrs,   \
@@ -405,6 +407,7 @@ static void launch_one_d(const Plan& p, const OnePlan& one, const DevView& v, hi
     switch (one.conf.kind) {
         case ONE_LB4: launch_one<DT, 4, 1, 32, 4>(p, one, v, stream); break;
         case ONE_U4: launch_one<DT, 16, 4, 4, 1>(p, one, v, stream); break;
+        case ONE_U8: launch_one<DT, 16, 8, 2, 1>(p, one, v, stream); break;
         case ONE_U16: launch_one<DT, 16, 16, 1, 1>(p, one, v, stream); break;
         case ONE_TEAM4: launch_team<DT, 4, 16>(p, one, v, stream); break;
         case ONE_TEAM16: launch_team<DT, 16, 8>(p, one, v, stream); break;

@@ -237,12 +237,19 @@ constexpr int64_t kOneMaxSegs = int64_t(1) << 16;
 constexpr int64_t kOneMaxWords = int64_t(1) << 20;
 constexpr int64_t kOneMaxWork = int64_t(1) << 22;
 // Tiles of 64 16-byte vectors (1 KiB of a buffer) up to which lanes take 4
-// bytes, from which U is 4 and 16, and the wavefronts up to which such a launch
-// is resident at once (one_config).
+// bytes.
 constexpr int64_t kOneNarrowTiles = 512;
-constexpr int64_t kOneMinU4 = 3072;
-constexpr int64_t kOneMinU16 = 7168;
-constexpr int64_t kOneMaxResident = 2048;
+// Launches of more tiles than kOneManyTiles run in many rounds: tile after
+// tile, and with LDS asked for that nothing uses (kOneStreamLds), so that 20
+// (n = 2), 16 (n = 4 to 7) or 12 (n >= 8) wavefronts run on a compute unit.
+// us, an eighth of the tiles on each XCD and no limit / tile after tile and
+// 12 / 16 / 20: n = 4 fp32 over 2^26 364 / 364 / 341 / 338, over 2^27 724 /
+// 714 / 675 / 673; n = 6 over 43690368 (XCDs and 12: 358) / 339 / 325 / 331;
+// n = 8 over 2^25 362 / 349 / 355 / 360, over 2^26 725 / 712 / 736 / 744;
+// n = 3 over 89478336 361 / 465 / 377 / 357, no limit 334; n = 8 over 2^23,
+// 32768 tiles, 94 / 96 / 102 / 103.
+constexpr int64_t kOneManyTiles = 32768;
+constexpr int32_t one_lds(int32_t n) { return n == 2 ? 8192 : n == 3 ? 0 : n < 8 ? 10240 : 13312; }
 // Of kOneTeamMinN buffers and more, those up to which a workgroup takes a tile
 // of 4-byte lanes (onepass_team_kernel): of 16 waves while each compute unit
 // has one such tile (half as many again for kOneTeamManyN buffers), else of
@@ -410,7 +417,7 @@ struct SliceDesc {
 
 // The one-pass form of the whole plan (onepass.cpp): the segments, their
 // leaves, the tiling and the kernel instance.
-enum OneKind { ONE_LB4, ONE_U1B4, ONE_U1B8, ONE_U1B16, ONE_U4, ONE_U16, ONE_TEAM4, ONE_TEAM16 };
+enum OneKind { ONE_LB4, ONE_U1B4, ONE_U1B8, ONE_U1B16, ONE_U4, ONE_U8, ONE_U16, ONE_TEAM4, ONE_TEAM16 };
 struct OneConf {
     int32_t kind;            // OneKind
     int32_t lb, u, waves;    // bytes of a vector, vectors per lane, waves per workgroup
@@ -419,6 +426,7 @@ struct OnePlan {
     bool tried = false;      // built, or found to have none
     bool ok = false;         // every buffer ends with one value at every position
     bool chain = false;      // a chain of bf16 steps
+    bool many = false;       // runs in many rounds (kOneManyTiles)
     int32_t pushes = 0;      // most sums put aside in a segment
     OneConf conf{};
     int32_t depth = 0;       // sums put aside at once
@@ -523,12 +531,39 @@ void build_resident(const Plan& p, const ExecState& ex, SliceDesc& sd);
 // The one-pass form of the plan's executed phases, built on the first call;
 // one.ok stays false when there is none (onepass.cpp).
 void build_onepass(const Plan& p, const ExecState& ex, OnePlan& one);
-OneConf one_config(int32_t n, int64_t tiles16, int32_t depth, int32_t dtype);
+// The instances with U > 1: from how many tiles up to how many (chain: a chain
+// of bf16 steps too).  us at U 1 / 4 / 8 / 16, the (8, 3) tree over 24 buffers:
+// fp32 4096 tiles 36.6 / 33.7 / 34.8 / 35.0, 6144 55.9 / 54.0 / 50.3 / 51.9,
+// 7168 65.8 / 66.0 / 61.9 / 59.1, 12288 114 / 114 / 106 / 102; bf16 4096
+// 36.2 / 33.8 / 35.8 / 54.0, 6144 56.0 / 53.6 / 49.3 / 66.6, 12288 116 / 114 /
+// 111 / 102; Ring n = 17 fp32 20000 148 / 141 / 136 / 132.  With fewer buffers
+// than kOneWideMinN the reads are over too soon for it to matter (n = 4 fp32
+// 4097 tiles 7.3 / 7.8).
+struct OneWide {
+    bool bf16;
+    OneKind kind;
+    int32_t u;
+    int64_t from, to;
+    bool chain;
+};
+constexpr OneWide kOneWide[] = {
+    {false, ONE_U4, 4, 3072, 4607, true},    {false, ONE_U8, 8, 4608, 7167, true},
+    {false, ONE_U16, 16, 7168, 32768, true}, {true, ONE_U4, 4, 3072, 4607, true},
+    {true, ONE_U8, 8, 4608, 7372, true},     {true, ONE_U16, 16, 7373, 14746, false}};
+constexpr int32_t kOneWideMinN = 12;
+OneConf one_config(int32_t n, int64_t tiles16, int32_t depth, int32_t dtype, bool chain);
 // Its predicted time, ns, and whether its bytes take more of it than a
 // wavefront's work.  Of a form not built yet, a lower bound, and whether they
 // may.
 double onepass_time(const Plan& p, const OnePlan& one);
 bool onepass_streams(const Plan& p, const OnePlan& one);
+// Is the form faster than the resident one where both stream?  At U 1, below
+// kOneManyTiles and from kOneRowsMinN buffers on (the resident form then has
+// four waves a tile) it is not (RHD n = 32 fp32 over 8388608 resident 372 us,
+// one-pass 395, over 5120000 243 and 257; n = 8 over 8388608 113 and 94, over
+// 8389120 91 and 93).
+constexpr int32_t kOneRowsMinN = 20;
+bool onepass_beats_rows(const Plan& p, const OnePlan& one);
 // Does the one-pass form of a plan run as teams?
 bool onepass_teams(const Plan& p);
 

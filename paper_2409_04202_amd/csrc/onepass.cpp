@@ -94,10 +94,6 @@ struct Emit {
 
 }  // namespace
 
-// Instance and tile for `tiles16` tiles of 64 16-byte vectors (see
-// onepass.hpp for what was measured).  A wave's sums put aside take
-// depth * U * 64 sums of LDS; instances with U > 1 are for launches that are
-// resident at once, so they must fit beside each other.
 static bool team_tiles(int32_t n, int64_t tiles16) {
     return n >= kOneTeamMinN && tiles16 <= kOneTeamTiles;
 }
@@ -105,21 +101,26 @@ static int64_t tiles_of(const Plan& p) {  // of 1 KiB of a buffer
     return (p.N * p.esize + 1023) / 1024;
 }
 bool onepass_teams(const Plan& p) { return team_tiles(p.n, tiles_of(p)); }
-OneConf one_config(int32_t n, int64_t tiles16, int32_t depth, int32_t dtype) {
-    const int64_t sum = dtype == AR_BF16 ? 2 : 1;  // bytes of a sum per byte of elements
-    auto resident = [&](int64_t u) {
-        const int64_t units = (tiles16 + u - 1) / u;
-        const int64_t lds = depth * u * 1024 * sum;
-        return units <= kOneMaxResident &&
-               (lds == 0 || units <= kNumCUs * (kLdsBytesPerCU / lds));
-    };
+// Instance and tile for `tiles16` tiles of 64 16-byte vectors (see
+// onepass.hpp for what was measured).  Instances with U > 1 are for launches
+// that are resident at once, which their wavefronts' registers limit (kOneWide)
+// and, at a fifth less than would fit, the sums that they put aside in LDS,
+// depth * U * 64 each.
+OneConf one_config(int32_t n, int64_t tiles16, int32_t depth, int32_t dtype, bool chain) {
+    const bool bf16 = dtype == AR_BF16;
     if (team_tiles(n, tiles16)) {
         const int64_t one_a_unit = n >= kOneTeamManyN ? kOneTeam16Tiles * 3 / 2 : kOneTeam16Tiles;
         return {tiles16 <= one_a_unit ? ONE_TEAM16 : ONE_TEAM4, 4, 1, 1};
     }
     if (tiles16 <= kOneNarrowTiles) return {ONE_LB4, 4, 1, 4};
-    if (tiles16 >= kOneMinU16 && resident(16)) return {ONE_U16, 16, 16, 1};
-    if (tiles16 >= kOneMinU4 && tiles16 < kOneMinU16 && resident(4)) return {ONE_U4, 16, 4, 1};
+    if (n >= kOneWideMinN)
+        for (const OneWide& w : kOneWide) {
+            if (bf16 != w.bf16 || tiles16 < w.from || tiles16 > w.to || (chain && !w.chain)) continue;
+            const int64_t units = (tiles16 + w.u - 1) / w.u;
+            const int64_t lds = int64_t(depth) * w.u * 1024 * (bf16 ? 2 : 1);
+            if (lds == 0 || units * 5 <= kNumCUs * (kLdsBytesPerCU / lds) * 4)
+                return {w.kind, 16, w.u, 1};
+        }
     return {n < 8 ? ONE_U1B4 : n < 16 ? ONE_U1B8 : ONE_U1B16, 16, 1, 1};
 }
 
@@ -193,7 +194,8 @@ static void build(const Plan& p, const ExecState& ex, OnePlan& one) {
         one.chain = one.chain || (p.dtype == AR_BF16 && em.max_depth == 0 && w.size() > 2 &&
                                   (w[1] & kOneRound) != 0);
     }
-    one.conf = one_config(n, tiles_of(p), one.depth, p.dtype);
+    one.conf = one_config(n, tiles_of(p), one.depth, p.dtype, one.chain);
+    one.many = one.conf.u == 1 && one.conf.lb == 16 && one.cm && tiles_of(p) > kOneManyTiles;
     const int64_t vec = one.conf.lb / p.esize;
     const int64_t te = 64 * vec * one.conf.u;
     std::vector<int64_t> nt;
@@ -250,6 +252,11 @@ double onepass_time(const Plan& p, const OnePlan& one) {
 }
 bool onepass_streams(const Plan& p, const OnePlan& one) {
     return one_mem_time(p) >= one_wave_time(p, one);
+}
+
+bool onepass_beats_rows(const Plan& p, const OnePlan& one) {
+    return one.conf.u > 1 || one.conf.lb < 16 || !one.cm || one.many ||
+           p.n < kOneRowsMinN || tiles_of(p) <= kOneManyTiles / 2;
 }
 
 }  // namespace arp

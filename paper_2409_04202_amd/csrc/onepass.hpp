@@ -53,12 +53,15 @@ namespace arp {
 //    step and end together), with as many leaves in a batch as n gives it
 //    registers for no more (n = 3 over 2000003 fp32: B 4 9.0 us, B 16 11.3;
 //    RHD n = 8 over 2^26: B 8 716, B 4 743);
-//  * LB 16, U 4 or 16 where that still makes 768 to 2048 wavefronts: the
-//    whole launch is then resident at once, so that the chip first reads and
+//  * LB 16, U 4, 8 (bf16) or 16 where that still makes 512 to 2048 wavefronts:
+//    the whole launch is then resident at once, so that the chip first reads and
 //    then writes, and each buffer is touched in 4 or 16 KiB pieces (Ring
 //    n = 64 over 2^20 fp32: U 1 97 us, U 4 91; tree (8, 8) over 2^22: U 1
-//    386, U 16 357).  Larger ones run in many rounds anyhow and stream best
-//    with U 1 (RHD n = 8 over 2^26: U 1 716, U 4 782, U 16 846).
+//    386, U 16 357; bf16, whose sums take twice the registers, U 1 192, U 8
+//    187, U 16 209).  Larger ones run in many rounds anyhow and stream best
+//    with U 1 (RHD n = 8 over 2^26: U 1 716, U 4 782, U 16 846), tile after
+//    tile instead of an eighth of the vector on each XCD (eight times as many
+//    streams), and with fewer wavefronts a compute unit than fit (one_lds).
 constexpr uint32_t kOnePush = 1u << 16;
 constexpr uint32_t kOneRound = 1u << 17;
 constexpr int kOnePopShift = 24;
@@ -270,7 +273,7 @@ struct OnePass {
 // segment's end do nothing).  ptab: the n buffer pointers.  CM: bit 0
 // nontemporal loads, bit 1 nontemporal stores.  The grid is 8 * per_xcd:
 // workgroups go to the eight XCDs in turn, and each runs a contiguous eighth
-// of the tiles.  (per_xcd is an argument: a kernel that reads gridDim takes
+// of the tiles; per_xcd = 0: tile after tile, whatever the XCD.  (per_xcd is an argument: a kernel that reads gridDim takes
 // the 256 bytes of implicit arguments, 1 us more a launch on the host.)
 template <int DT, int LB, int U, int B, int W, int CM>
 __global__ __launch_bounds__(64 * W) void onepass_kernel(
@@ -285,7 +288,7 @@ __global__ __launch_bounds__(64 * W) void onepass_kernel(
     constexpr int VEC = K::VEC;
     constexpr int64_t TE = int64_t(64) * U * VEC;  // elements of a tile
     const int lane = int(threadIdx.x) & 63;
-    const uint32_t b = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+    const uint32_t b = per_xcd ? (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3) : blockIdx.x;
     const uint32_t unit = b * W + uint32_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)));
     if (unit >= nunits) return;
     uint32_t s = 0, t = unit;

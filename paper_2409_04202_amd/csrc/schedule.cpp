@@ -633,7 +633,8 @@ ExecState* exec_state(Plan& p) {
                         ex->one_aligned = onepass_time(p, ex->one) < t && one_time() < t;
                     else
                         ex->one_aligned = onepass_streams(p, ex->one) && one_time() >= 0.0 &&
-                                          ex->one.ok && onepass_streams(p, ex->one);
+                                          ex->one.ok && onepass_streams(p, ex->one) &&
+                                          (!sd.resident || onepass_beats_rows(p, ex->one));
                 }
                 sd.cuts_base = ex->slices.empty() ? 0
                                                   : ex->slices.back().cuts_base +

@@ -38,7 +38,7 @@ def test_program_and_tiles(kind, n, fan, dtype):
     kib = 1024 // es
     for N in (16 // es + 1, 67, max(n + 1, 16 // es), 64 * 4 // es + 1, 5 * n + 3, 64 * kib + 1,
               200 * kib - 1, 513 * kib - 1, 3072 * kib + 3,
-              7168 * kib + 5):
+              4608 * kib + 1, 7168 * kib + 5):
         with check.Plan(n, N, dtype, kind, fan) as p:
             L = p.launches()
             if n <= 512 and N % n:
@@ -86,7 +86,12 @@ GPU = [("ring", 5, 67, "f32", None), ("rhd", 5, 4099, "f32", None), ("rhd", 7, 4
        ("tree", 20, 64 * 256 - 1, "f32", (4, 5)), ("ring", 129, 96 * 512 + 1, "bf16", None),
        ("tree", 130, 97 * 256 + 1, "f32", (10, 13)), ("rhd", 66, 200 * 512 - 3, "bf16", None),
        ("cps", 21, 200 * 256 + 3, "i32", None), ("rhd", 300, 4099, "f32", None),
-       ("rhd", 4, 7168 * 1024 + 3, "f32", None), ("cps", 2, 2049 * 16 * 512 + 5, "bf16", None)]
+       ("rhd", 4, 7168 * 1024 + 3, "f32", None), ("cps", 2, 2049 * 16 * 512 + 5, "bf16", None),
+       # U 4, 8 and 16 (from 12 buffers on), tile after tile beyond 32768 tiles
+       ("cps", 12, 3072 * 256 + 5, "f32", None), ("tree", 12, 4608 * 256 + 3, "i32", (4, 3)),
+       ("rhd", 12, 7168 * 256 + 9, "f32", None), ("tree", 12, 3100 * 512 + 1, "bf16", (4, 3)),
+       ("ring", 13, 4608 * 512 + 7, "bf16", None), ("cps", 12, 7373 * 512 + 3, "bf16", None),
+       ("rhd", 3, 32769 * 256 + 5, "f32", None)]
 
 
 def _oracle_plan(kind, n, N, fan):
