@@ -228,10 +228,11 @@ ar_status ar_plan_execute_timed(ar_plan* plan, void* const* bufs,
  * set (the staging ar_plan_execute allocates per plan) live instead in one
  * array of AR_NOALLOC_MAX_BYTES bytes that the library holds on every device
  * it runs on, from that device's first such call until the process ends.
- *   - Every call on a device shares that device's array, which keeps the last
- *     call's contents: the call copies the plan's tables and records into it
- *     (hipMemcpyAsync from host memory the plan owns, on `stream`) unless the
- *     last call on the device used the same plan, options and buffer set.
+ *   - Every call on a device shares that device's array, which keeps what
+ *     the last calls put there, each plan at a place of its own, until a later
+ *     call needs the space: the call copies the plan's tables and records into
+ *     it (hipMemcpyAsync from host memory the plan owns, on `stream`) unless
+ *     it still holds those of this plan, its options and this buffer set.
  *     Calls that may overlap on one device (other streams, other host
  *     threads without ordering) race on the array and must be ordered by
  *     the caller.

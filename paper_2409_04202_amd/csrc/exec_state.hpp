@@ -471,6 +471,7 @@ struct ExecState {
     std::vector<uint64_t> img;
     int64_t img_off[8] = {};     // byte offsets: tiles, cuts, sched_off,
                                  // sched, stiles, runits, prog, records
+    int64_t scratch_off[2] = {-1, -1};  // places in the array: img, one_img
     std::vector<uint64_t> one_img;  // the same for the one-pass launch
     int64_t one_img_off[4] = {};    // segments, leaves, tiles, buffer pointers
 };

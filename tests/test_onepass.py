@@ -159,3 +159,38 @@ def test_dense_rows_leave_their_surroundings_alone(dtype):
                 assert torch.equal(torch.isnan(a), nan)
                 bits = torch.int32 if dtype == "f32" else torch.int16
                 assert torch.equal(a.view(bits)[~nan], b.view(bits)[~nan])
+
+
+@pytest.mark.gpu
+def test_many_plans_share_the_no_allocation_array():
+    # 20 plans of 2 MiB of records each (Ring over 128 buffers as written)
+    # in turn: their images go round the 32 MiB array; a graph of the first
+    # one replays after an uncaptured call has put its tables back
+    n, N = 128, 1024
+    xs0 = workloads.draw(n, N, "i32", "int1000", 3)
+    ref, got = to_device(xs0, "i32"), to_device(xs0, "i32")
+    s = torch.cuda.current_stream()
+    plans = [arplan.Plan(n, N, "i32", "ring") for _ in range(20)]
+    for p in plans:
+        p.set_option(arplan.AR_OPT_FUSE, 0)
+        p.set_option(arplan.AR_OPT_SLICE, 0)
+    plans[0].execute_noalloc(got, s)
+    plans[0].execute(ref, s)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plans[0].execute_noalloc(got, torch.cuda.current_stream())
+    for rnd in range(2):
+        for i, p in enumerate(plans):
+            say("case: noalloc round %d plan %d" % (rnd, i))
+            p.execute_noalloc(got, s)
+            p.execute(ref, s)
+        plans[0].execute_noalloc(got, s)
+        plans[0].execute(ref, s)
+        torch.cuda.synchronize()
+        g.replay()
+        plans[0].execute(ref, s)
+        torch.cuda.synchronize()
+        assert all(np.array_equal(a, b) for a, b in zip(to_host(got, "i32"), to_host(ref, "i32"))), rnd
+    for p in plans:
+        p.close()
