@@ -11,7 +11,10 @@
 // cache keeps them per device, so repeated executes on the same buffers
 // launch kernels only.  The tile, sliced and resident tables are uploaded on
 // the first execute on a device.  Buffers that are not 16-byte aligned run
-// every phase as its phase launches.
+// every phase as its phase launches (phase_any_kernel when each is at its
+// element's alignment).  A plan that leaves one value in every buffer may
+// instead run as one launch of onepass_kernel or onepass_team_kernel, which
+// needs its own small tables and the buffer pointers alone.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -173,20 +176,22 @@ static ar_status check_buffers(const Plan& p, const std::vector<void*>& bufs) {
     return AR_OK;
 }
 
-static bool buffers_aligned(void* const* bufs, int32_t n) {
-    for (int32_t i = 0; i < n; ++i)
-        if (reinterpret_cast<uint64_t>(bufs[i]) & 15) return false;
-    return true;
+// What every buffer is aligned to: 16 bytes, its element (16-byte accesses at
+// element alignment), or less (element-wise).
+enum Align { ALIGN_NONE, ALIGN_ELEM, ALIGN_16 };
+static Align buffers_align(void* const* bufs, int32_t n, int32_t esize) {
+    uint64_t any = 0;
+    for (int32_t i = 0; i < n; ++i) any |= reinterpret_cast<uint64_t>(bufs[i]);
+    return !(any & 15) ? ALIGN_16 : !(any & uint64_t(esize - 1)) ? ALIGN_ELEM : ALIGN_NONE;
 }
 
 // Does a call on these buffers run the one-pass launch?  (Its form is built
 // here when only unaligned buffers take it.)
 static bool takes_one(const Plan& p, ExecState& ex, void* const* bufs) {
     if (!ex.one_aligned && !ex.one_unaligned) return false;
-    if (buffers_aligned(bufs, p.n)) return ex.one_aligned;
-    if (!ex.one_unaligned) return false;
-    for (int32_t i = 0; i < p.n; ++i)  // each at its element's alignment
-        if (reinterpret_cast<uint64_t>(bufs[i]) & uint64_t(p.esize - 1)) return false;
+    const Align a = buffers_align(bufs, p.n, p.esize);
+    if (a == ALIGN_16) return ex.one_aligned;
+    if (!ex.one_unaligned || a != ALIGN_ELEM) return false;
     build_onepass(p, ex, ex.one);
     return ex.one.ok;
 }
@@ -265,17 +270,19 @@ static ar_status step_records(const Plan& p, const ExecState& ex, DevState& d,
     v->key = bufs;
     v->valid = true;
     v->stamp = d.clock;
-    v->aligned = buffers_aligned(bufs.data(), p.n);
+    v->align = buffers_align(bufs.data(), p.n, p.esize);
     *out = v;
     return AR_OK;
 }
 
+// align: the buffers' (Align).
 template <int DT, int K>
-static void launch_dk(bool vecok, int cm, int64_t blocks, hipStream_t st,
+static void launch_dk(int align, int cm, int64_t blocks, hipStream_t st,
                       const uint64_t* recs, int64_t stride, const int2* tiles,
                       int64_t nunits, int64_t tps, int64_t te, int rtg,
                       int dsplit, int wide) {
     const dim3 block(64 * kcfg(K).WPB);
+    const bool vecok = align == ALIGN_16;
     if constexpr (K == 2) {
         if (wide && vecok && cm == 3 && dsplit == 1) {  // see kWideBytes
             hipLaunchKernelGGL((phase_kernel<DT, 2, true, 3, kWideU>),
@@ -318,7 +325,10 @@ static void launch_dk(bool vecok, int cm, int64_t blocks, hipStream_t st,
 #define AR_LAUNCH(V, C)                                                                \
     hipLaunchKernelGGL((phase_kernel<DT, K, V, C>), grid, block, 0, st, recs, stride, \
                        tiles, nunits, tps, te, rtg)
-    if (!vecok) AR_LAUNCH(false, 0);
+    if (align == ALIGN_ELEM)
+        hipLaunchKernelGGL((phase_any_kernel<DT, K>), grid, block, 0, st, recs, stride, tiles,
+                           nunits, tps, te);
+    else if (!vecok) AR_LAUNCH(false, 0);
     else if (cm == 0) AR_LAUNCH(true, 0);
     else if (cm == 1) AR_LAUNCH(true, 1);
     else if (cm == 2) AR_LAUNCH(true, 2);
@@ -327,18 +337,18 @@ static void launch_dk(bool vecok, int cm, int64_t blocks, hipStream_t st,
 }
 
 template <int DT>
-static void launch_d(int K, bool vecok, int cm, int64_t blocks, hipStream_t st,
+static void launch_d(int K, int align, int cm, int64_t blocks, hipStream_t st,
                      const uint64_t* recs, int64_t stride, const int2* tiles,
                      int64_t nunits, int64_t tps, int64_t te, int rtg,
                      int dsplit, int wide) {
     switch (K) {
-        case 1: launch_dk<DT, 1>(vecok, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        case 2: launch_dk<DT, 2>(vecok, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        case 3: launch_dk<DT, 3>(vecok, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        case 4: launch_dk<DT, 4>(vecok, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        case 8: launch_dk<DT, 8>(vecok, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        case 16: launch_dk<DT, 16>(vecok, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        default: launch_dk<DT, 0>(vecok, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
+        case 1: launch_dk<DT, 1>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
+        case 2: launch_dk<DT, 2>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
+        case 3: launch_dk<DT, 3>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
+        case 4: launch_dk<DT, 4>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
+        case 8: launch_dk<DT, 8>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
+        case 16: launch_dk<DT, 16>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
+        default: launch_dk<DT, 0>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
     }
 }
 
@@ -364,7 +374,7 @@ struct DevView {
     const ResUnit* runits;
     const uint32_t* prog;
     const uint64_t* recs;  // step records, then the n buffer pointers
-    bool aligned;          // every buffer 16-byte aligned
+    int align;             // the buffers' (Align)
     // the one-pass launch, when the call takes it: its tables, the pointers
     bool one = false;
     const OneSeg* one_segs = nullptr;
@@ -381,7 +391,7 @@ static void launch_one(const Plan& p, const OnePlan& one, const DevView& v, hipS
     const dim3 grid(many ? static_cast<uint32_t>(blocks) : per_xcd * 8), block(64 * W);
     const size_t lds = std::max(size_t(one.depth) * U * 64 * W * sizeof(typename OneVec<DT, LB>::Acc),
                                 many ? size_t(one_lds(p.n)) : size_t(0));
-    const int32_t amask = v.aligned ? LB / p.esize - 1 : 0;
+    const int32_t amask = v.align == ALIGN_16 ? LB / p.esize - 1 : 0;
 #define AR_ONE(CM)                                                                            \
     hipLaunchKernelGGL((onepass_kernel<DT, LB, U, B, W, CM>), grid, block, lds, stream, v.ptrs,   \
                        p.n, v.one_prog, v.one_segs, int32_t(one.segs.size()), v.one_tiles,    \
@@ -399,7 +409,7 @@ static void launch_team(const Plan& p, const OnePlan& one, const DevView& v, hip
     hipLaunchKernelGGL((onepass_team_kernel<DT, W, LPW>), dim3(per_xcd * 8), dim3(64 * W), lds, stream,
                        v.ptrs, p.n, v.one_prog, v.one_segs, int32_t(one.segs.size()), v.one_tiles,
                        uint32_t(one.nunits), uint32_t(one.tiles_per_seg), per_xcd, p.N,
-                       v.aligned ? 4 / p.esize - 1 : 0);
+                       v.align == ALIGN_16 ? 4 / p.esize - 1 : 0);
 }
 
 template <int DT>
@@ -425,7 +435,7 @@ static ar_status launch_all(ar_plan* plan, const ExecState* ex, const DevView& v
     {
         // sliced launches need 16-byte aligned buffers; otherwise every
         // phase runs as its phase launches
-        const bool staged = v.aligned;
+        const bool staged = v.align == ALIGN_16;
         const int64_t nlaunch = v.one ? 1
                                 : staged ? int64_t(ex->run_stages.size()) : int64_t(ex->launches.size());
         if (timer && timer->count + nlaunch > timer->cap)
@@ -522,17 +532,17 @@ static ar_status launch_all(ar_plan* plan, const ExecState* ex, const DevView& v
                 const int2* tiles = L.tile_off >= 0 ? d->tiles + L.tile_off : nullptr;
                 switch (plan->dtype) {
                     case AR_F32:
-                        launch_d<DT_F32>(L.kern_k, v.aligned, L.cm, blocks, stream, recs,
+                        launch_d<DT_F32>(L.kern_k, v.align, L.cm, blocks, stream, recs,
                                          L.rec_stride, tiles, L.nunits, L.tiles_per_step,
                                          L.tile_elems, L.rt_group, L.dsplit, L.wide);
                         break;
                     case AR_I32:
-                        launch_d<DT_I32>(L.kern_k, v.aligned, L.cm, blocks, stream, recs,
+                        launch_d<DT_I32>(L.kern_k, v.align, L.cm, blocks, stream, recs,
                                          L.rec_stride, tiles, L.nunits, L.tiles_per_step,
                                          L.tile_elems, L.rt_group, L.dsplit, L.wide);
                         break;
                     default:
-                        launch_d<DT_BF16>(L.kern_k, v.aligned, L.cm, blocks, stream, recs,
+                        launch_d<DT_BF16>(L.kern_k, v.align, L.cm, blocks, stream, recs,
                                           L.rec_stride, tiles, L.nunits, L.tiles_per_step,
                                           L.tile_elems, L.rt_group, L.dsplit, L.wide);
                         break;
@@ -562,7 +572,7 @@ static ar_status run(ar_plan* plan, const std::vector<void*>& bufs,
         s = step_records(*plan, *ex, *d, bufs, one, stream, &pe);
         if (s != AR_OK) return s;
         DevView v{d->tiles, d->cuts, d->sched_off, d->sched, d->stiles,
-                  d->runits, d->prog, pe->dev, pe->aligned};
+                  d->runits, d->prog, pe->dev, pe->align};
         if (one) {
             v.one = true;
             v.one_segs = d->one_segs;
@@ -768,7 +778,7 @@ AR_EXPORT ar_status ar_plan_execute_noalloc(ar_plan* plan, void* const* bufs, vo
         }
         if (one) {
             DevView v{};
-            v.aligned = buffers_aligned(bufs, plan->n);
+            v.align = buffers_align(bufs, plan->n, plan->esize);
             v.one = true;
             v.one_segs = reinterpret_cast<const OneSeg*>(base + ex->one_img_off[0]);
             v.one_prog = reinterpret_cast<const uint32_t*>(base + ex->one_img_off[1]);
@@ -782,7 +792,7 @@ AR_EXPORT ar_status ar_plan_execute_noalloc(ar_plan* plan, void* const* bufs, vo
                         reinterpret_cast<const int32_t*>(at(2)), reinterpret_cast<const int32_t*>(at(3)),
                         reinterpret_cast<const int2*>(at(4)), reinterpret_cast<const ResUnit*>(at(5)),
                         reinterpret_cast<const uint32_t*>(at(6)), reinterpret_cast<const uint64_t*>(at(7)),
-                        buffers_aligned(bufs, plan->n)};
+                        buffers_align(bufs, plan->n, plan->esize)};
         return launch_all(plan, ex, v, st, nullptr);
     } catch (const std::bad_alloc&) {
         return fail(AR_ERR_OOM, "host allocation failed");

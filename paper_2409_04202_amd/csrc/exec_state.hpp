@@ -343,7 +343,7 @@ struct PtrEntry {
     hipEvent_t done = nullptr;
     uint64_t stamp = 0;
     bool valid = false;
-    bool aligned = false;
+    int align = 0;  // the buffers' (Align, exec.hip)
 };
 
 struct DevState {

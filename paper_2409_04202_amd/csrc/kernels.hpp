@@ -646,6 +646,125 @@ __global__ __launch_bounds__(64 * kcfg(K).WPB) void phase_kernel(
     }
 }
 
+// phase_kernel for buffers that are not all 16-byte aligned but each at its
+// element's alignment: vectors are counted from the step's start and loaded
+// and stored with element alignment (the hardware takes 16-byte accesses at
+// such addresses); the last tile's remainder is done element-wise.  Element by
+// element, which buffers off their element's alignment still are
+// (phase_kernel with VECOK false), the loads of 256 or 128 bytes a wave were
+// what bound it.  us, as written, rows of one dense matrix, before and after:
+// co-located PS n = 16 over 1048581 fp32 50 -> 31, bf16 84 -> 31; RHD n = 8 over
+// 4194309 fp32 171 -> 106, bf16 190 -> 60, over 131075 bf16 149 -> 22; the
+// (8, 8) tree over 4194309 fp32 925 -> 598.
+constexpr int kAnyU = 4;  // vectors per lane and source of a pass, 2 from 8 sources on
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+template <int DT> struct AnyVec { using M = u32x4_a4; };
+template <> struct AnyVec<DT_BF16> { using M = u32x4_a2; };
+
+template <int DT, int K, int U, bool FULL>
+__device__ __forceinline__ void fold_any(void* const* __restrict__ sp, int k,
+                                         void* const* __restrict__ dp, int ndst, int64_t e0,
+                                         int64_t nv, int lane) {
+    using T = typename Elem<DT>::T;
+    using M = typename AnyVec<DT>::M;
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) ok[u] = FULL || u * 64 + lane < nv;
+    auto row = [&](void* b) { return (AR_GLOBAL M*)(as_global<T>(b) + e0) + lane; };
+    u32x4 out[U];
+    if constexpr (K > 0) {
+        u32x4 x[K][U];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const AR_GLOBAL M* s = row(sp[j]);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (ok[u]) x[j][u] = s[u * 64];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if constexpr (K == 1) {
+                out[u] = x[0][u];
+            } else {
+                VAcc<DT> acc;
+                acc.init(x[0][u]);
+#pragma unroll
+                for (int j = 1; j < K; ++j) acc.add(x[j][u]);
+                out[u] = acc.out();
+            }
+        }
+    } else if (k == 1) {
+        const AR_GLOBAL M* s = row(sp[0]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (ok[u]) out[u] = s[u * 64];
+    } else {
+        VAcc<DT> acc[U];
+        for (int j0 = 0; j0 < k; j0 += kRtGroup) {
+            u32x4 x[kRtGroup][U];
+#pragma unroll
+            for (int g = 0; g < kRtGroup; ++g)
+                if (j0 + g < k) {  // wave-uniform
+                    const AR_GLOBAL M* s = row(sp[j0 + g]);
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (ok[u]) x[g][u] = s[u * 64];
+                }
+#pragma unroll
+            for (int g = 0; g < kRtGroup; ++g)
+                if (j0 + g < k) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (j0 + g == 0) acc[u].init(x[g][u]);
+                        else acc[u].add(x[g][u]);
+                    }
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) out[u] = acc[u].out();
+    }
+    for (int j = 0; j < ndst; ++j) {
+        AR_GLOBAL M* d = row(dp[j]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (ok[u]) d[u * 64] = out[u];
+    }
+}
+
+template <int DT, int K>
+__global__ __launch_bounds__(64 * kcfg(K).WPB) void phase_any_kernel(
+    const uint64_t* __restrict__ recs, int64_t stride, const int2* __restrict__ tiles,
+    int64_t nunits, int64_t tiles_per_step, int64_t tile_elems) {
+    constexpr int VEC = Elem<DT>::VEC;
+    constexpr int U = K >= 8 || K == 0 ? kAnyU / 2 : kAnyU;
+    const int lane = int(threadIdx.x) & 63;
+    const int64_t unit = int64_t(blockIdx.x) * kcfg(K).WPB +
+                         int64_t(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    if (unit >= nunits) return;
+    int64_t s, t;
+    unit_tile(unit, tiles, tiles_per_step, s, t);
+    s = uniform64(s);
+    t = uniform64(t);
+    if (s < 0) return;  // a padding entry of a tile table
+    const uint64_t* rec = recs + s * stride;
+    const StepHead st = *reinterpret_cast<const StepHead*>(rec);
+    const int k = K ? K : st.k;
+    void* const* sp = reinterpret_cast<void* const*>(rec + kRecHead);
+    void* const* dp = sp + k;
+    // elements [lo, hi) of the step; whole vectors from lo, then the rest
+    const TileSpan ts = tile_span(st.begin, st.end, t, tile_elems, VEC, false);
+    if (ts.lo >= ts.hi) return;
+    const int64_t nv = (ts.hi - ts.lo) / VEC;
+    int64_t at = 0;
+    for (; at + 64 * U <= nv; at += 64 * U)
+        fold_any<DT, K, U, true>(sp, k, dp, st.ndst, ts.lo + at * VEC, 64 * U, lane);
+    if (at < nv)
+        fold_any<DT, K, U, false>(sp, k, dp, st.ndst, ts.lo + at * VEC, nv - at, lane);
+    if (ts.lo + nv * VEC < ts.hi)
+        fold_scalar<DT, K>(sp, k, dp, st.ndst, ts.lo + nv * VEC, ts.hi, lane);
+}
+
 // Split launch (see split_tile): workgroup b runs wave tile b of the
 // launch's tile table (tiles[b] = (step, tile in step), or (-1, 0) padding),
 // its kSplitWaves waves each storing to a share of the destinations.

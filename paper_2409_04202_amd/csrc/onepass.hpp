@@ -99,8 +99,6 @@ __host__ __device__ __forceinline__ OneLane one_lane(int64_t t0, int64_t e, int6
 
 // LB bytes of elements as a lane holds them (V), as they lie in memory (M:
 // element alignment), and their sum.
-typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32_a2 __attribute__((aligned(2)));
 template <int DT, int LB> struct OneVec;
 template <int DT> struct OneVec<DT, 16> { using V = u32x4; using M = u32x4_a4; using Acc = VAcc<DT>; };

@@ -194,3 +194,27 @@ def test_many_plans_share_the_no_allocation_array():
         assert all(np.array_equal(a, b) for a, b in zip(to_host(got, "i32"), to_host(ref, "i32"))), rnd
     for p in plans:
         p.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "i32"])
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 8, 12, 16])
+def test_phase_launches_on_element_aligned_buffers(n, dtype):
+    # every source count's kernel, on rows each at another alignment, as
+    # written (co-located PS: an n-way fold and copies, n ragged blocks) and
+    # with the rewrites (many destinations); around a pass of 64 lanes x 2 or 4
+    # vectors and a tile
+    vec = 8 if dtype == "bf16" else 4
+    for N in (n + 1, 64 * vec * 2 * n + 1, 64 * vec * 4 * n - 1, 1024 * vec * n + 5):
+        xs0 = workloads.draw(n, N, dtype, "int1000" if dtype == "i32" else "uniform", N % 97)
+        want = oracle.execute(oracle.make_plan("cps", n, N, None), [x.copy() for x in xs0], dtype)
+        for fuse in (0, 1):
+            say("case: element-aligned phases cps n=%d N=%d %s fuse=%d" % (n, N, dtype, fuse))
+            ts = [to_device([x], dtype, 1 + q % (vec - 1))[0] for q, x in enumerate(xs0)]
+            with arplan.Plan(n, N, dtype, "cps") as p:
+                p.set_option(arplan.AR_OPT_FUSE, fuse)
+                p.set_option(arplan.AR_OPT_SLICE, 0)
+                run_plan(p, ts)
+            got = to_host(ts, dtype)
+            for q in range(n):
+                assert np.array_equal(got[q], want[q]), (N, fuse, q)
