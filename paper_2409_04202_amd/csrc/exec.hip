@@ -280,7 +280,7 @@ template <int DT, int K>
 static void launch_dk(int align, int cm, int64_t blocks, hipStream_t st,
                       const uint64_t* recs, int64_t stride, const int2* tiles,
                       int64_t nunits, int64_t tps, int64_t te, int rtg,
-                      int dsplit, int wide) {
+                      int dsplit, int wide, int narrow) {
     const dim3 block(64 * kcfg(K).WPB);
     const bool vecok = align == ALIGN_16;
     if constexpr (K == 2) {
@@ -322,6 +322,8 @@ static void launch_dk(int align, int cm, int64_t blocks, hipStream_t st,
         blocks = (nunits + kcfg(K).WPB - 1) / kcfg(K).WPB;
     }
     const dim3 grid(static_cast<uint32_t>(blocks));
+    constexpr int kCachedU = K == 1 ? kNarrowU1 : 0;  // see kNarrowMinSrc
+    constexpr int kNarrowU = K == 0 ? kNarrowU0 : kCachedU;
 #define AR_LAUNCH(V, C)                                                                \
     hipLaunchKernelGGL((phase_kernel<DT, K, V, C>), grid, block, 0, st, recs, stride, \
                        tiles, nunits, tps, te, rtg)
@@ -329,7 +331,12 @@ static void launch_dk(int align, int cm, int64_t blocks, hipStream_t st,
         hipLaunchKernelGGL((phase_any_kernel<DT, K>), grid, block, 0, st, recs, stride, tiles,
                            nunits, tps, te);
     else if (!vecok) AR_LAUNCH(false, 0);
-    else if (cm == 0) AR_LAUNCH(true, 0);
+    else if (cm == 0 && narrow)
+        hipLaunchKernelGGL((phase_kernel<DT, K, true, 0, kNarrowU>), grid, block, 0, st, recs,
+                           stride, tiles, nunits, tps, te, rtg);
+    else if (cm == 0)
+        hipLaunchKernelGGL((phase_kernel<DT, K, true, 0, kCachedU>), grid, block, 0, st, recs,
+                           stride, tiles, nunits, tps, te, rtg);
     else if (cm == 1) AR_LAUNCH(true, 1);
     else if (cm == 2) AR_LAUNCH(true, 2);
     else AR_LAUNCH(true, 3);
@@ -340,15 +347,15 @@ template <int DT>
 static void launch_d(int K, int align, int cm, int64_t blocks, hipStream_t st,
                      const uint64_t* recs, int64_t stride, const int2* tiles,
                      int64_t nunits, int64_t tps, int64_t te, int rtg,
-                     int dsplit, int wide) {
+                     int dsplit, int wide, int narrow) {
     switch (K) {
-        case 1: launch_dk<DT, 1>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        case 2: launch_dk<DT, 2>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        case 3: launch_dk<DT, 3>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        case 4: launch_dk<DT, 4>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        case 8: launch_dk<DT, 8>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        case 16: launch_dk<DT, 16>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
-        default: launch_dk<DT, 0>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide); break;
+        case 1: launch_dk<DT, 1>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide, narrow); break;
+        case 2: launch_dk<DT, 2>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide, narrow); break;
+        case 3: launch_dk<DT, 3>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide, narrow); break;
+        case 4: launch_dk<DT, 4>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide, narrow); break;
+        case 8: launch_dk<DT, 8>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide, narrow); break;
+        case 16: launch_dk<DT, 16>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide, narrow); break;
+        default: launch_dk<DT, 0>(align, cm, blocks, st, recs, stride, tiles, nunits, tps, te, rtg, dsplit, wide, narrow); break;
     }
 }
 
@@ -534,17 +541,20 @@ static ar_status launch_all(ar_plan* plan, const ExecState* ex, const DevView& v
                     case AR_F32:
                         launch_d<DT_F32>(L.kern_k, v.align, L.cm, blocks, stream, recs,
                                          L.rec_stride, tiles, L.nunits, L.tiles_per_step,
-                                         L.tile_elems, L.rt_group, L.dsplit, L.wide);
+                                         L.tile_elems, L.rt_group, L.dsplit, L.wide,
+                                         L.narrow);
                         break;
                     case AR_I32:
                         launch_d<DT_I32>(L.kern_k, v.align, L.cm, blocks, stream, recs,
                                          L.rec_stride, tiles, L.nunits, L.tiles_per_step,
-                                         L.tile_elems, L.rt_group, L.dsplit, L.wide);
+                                         L.tile_elems, L.rt_group, L.dsplit, L.wide,
+                                         L.narrow);
                         break;
                     default:
                         launch_d<DT_BF16>(L.kern_k, v.align, L.cm, blocks, stream, recs,
                                           L.rec_stride, tiles, L.nunits, L.tiles_per_step,
-                                          L.tile_elems, L.rt_group, L.dsplit, L.wide);
+                                          L.tile_elems, L.rt_group, L.dsplit, L.wide,
+                                          L.narrow);
                         break;
                 }
             }

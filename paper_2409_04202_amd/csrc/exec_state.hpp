@@ -46,6 +46,19 @@ constexpr int64_t kFineTileMinBytes = int64_t(2) << 20;
 // (kWideU8 vectors per lane and source: 198 -> 196 us for the (8, 8) tree's
 // 1.1 GiB first level; bf16 folds ran 3 % slower with it).
 constexpr int64_t kWideBytes = int64_t(512) << 20;
+// A launch below kNtBytes stays in the caches and is bound by latency: more
+// wavefronts in flight, with the registers of fewer vectors, serve it better.
+// Its copies make passes of kNarrowU1 vectors a lane, and its runtime-source-
+// count folds of kNarrowMinSrc and more sources passes of kNarrowU0.  us, as
+// written, fp32 unless said: co-located PS n = 12 over 2^16 10.6 -> 9.7, n = 24
+// over 2^18 25.0 -> 20.1, n = 32 over 2^18 33.4 -> 28.1, n = 24 bf16 over 2^20
+// 37.7 -> 35.3, n = 12 over 2^20 37.0 -> 36.5; copies alone: RHD n = 8 over
+// 2^20 31.2 -> 30.0, Ring n = 16 over 2^22 280 -> 266, the (8, 8) tree over 2^18
+// 34.8 -> 35.1.
+// Folds of 6 sources lost (9.2 -> 9.5 at 2^16 fp32, 25.9 -> 27.9 at 2^22
+// bf16), and so did larger launches of either kind, which stream (RHD n = 8
+// over 2^26 1496 -> 1567, co-located PS n = 32 over 2^22 172 -> 205).
+constexpr int kNarrowMinSrc = 8;
 // A runtime-source-count launch (a fan-in without an unrolled kernel)
 // moving less than kRtGroupMaxBytes keeps the loads of kRtGroup sources in
 // flight together; larger ones load one source at a time (measured: k = 24
@@ -328,6 +341,7 @@ struct LaunchDesc {
     int32_t dsplit;          // waves per tile (split_tile), 1: one
     int32_t affinity;        // 1: the tile table places tiles by xcd_of
     int32_t wide;            // 1: the wide 2-source instance (kWideU per pass)
+    int32_t narrow;          // 1: the narrow runtime-k instance (kNarrowU0)
     int64_t bytes;           // (k + destinations) * len * e over the steps
     int64_t hbm;             // predicted HBM traffic: bytes, less the repeated
                              // reads of a range by the launch's copies

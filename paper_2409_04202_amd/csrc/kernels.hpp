@@ -71,6 +71,8 @@ struct KCfg {
 };
 constexpr int kWideU = 16;   // vectors per lane and source of the wide 2-source pass
 constexpr int kWideU8 = 4;   // ... and of the wide 8-source pass (4-byte elements)
+constexpr int kNarrowU1 = 4; // ... of the narrow copy pass
+constexpr int kNarrowU0 = 2; // ... of the narrow runtime-source-count pass
 __host__ __device__ constexpr KCfg kcfg(int K) {
     return K == 1 ? KCfg{16, 8, 1024}
          : K == 2 ? KCfg{8, 8, 1024}

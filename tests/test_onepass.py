@@ -218,3 +218,27 @@ def test_phase_launches_on_element_aligned_buffers(n, dtype):
             got = to_host(ts, dtype)
             for q in range(n):
                 assert np.array_equal(got[q], want[q]), (N, fuse, q)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "i32"])
+@pytest.mark.parametrize("n", [7, 9, 12, 17, 31])
+def test_narrow_passes_of_small_launches(n, dtype):
+    # runtime source counts on both sides of the narrow pass's first one, and
+    # copies, as written: around a fold pass of 64 lanes x 2 vectors, a copy
+    # pass of 64 x 4 and a tile (blocks of 16-byte aligned length and not)
+    vec = 8 if dtype == "bf16" else 4
+    for blk in (vec, 64 * vec * 2, 64 * vec * 2 + vec, 64 * vec * 4 - vec, 1024 * vec + vec):
+        for N in (n * blk, n * blk - 3):
+            xs0 = workloads.draw(n, N, dtype, "int1000" if dtype == "i32" else "uniform", N % 97)
+            want = oracle.execute(oracle.make_plan("cps", n, N, None),
+                                  [x.copy() for x in xs0], dtype)
+            say("case: narrow passes cps n=%d N=%d %s" % (n, N, dtype))
+            ts = to_device(xs0, dtype)
+            with arplan.Plan(n, N, dtype, "cps") as p:
+                p.set_option(arplan.AR_OPT_FUSE, 0)
+                p.set_option(arplan.AR_OPT_SLICE, 0)
+                run_plan(p, ts)
+            got = to_host(ts, dtype)
+            for q in range(n):
+                assert np.array_equal(got[q], want[q]), (N, q)
