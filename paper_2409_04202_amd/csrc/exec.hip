@@ -627,6 +627,7 @@ struct ScratchImage {
 };
 struct ScratchDev {
     uint8_t* ptr = nullptr;       // device address of `scratch` on this device
+    uint64_t last = 0;            // serial of the last call's executor state
     std::vector<ScratchImage> held;
 };
 // Images kept at most: a program's plans in turn; each call looks through them.
@@ -636,6 +637,12 @@ std::vector<ScratchDev> g_scratch;  // by device ordinal
 int64_t g_scratch_next = 0;         // where the next image is placed
 
 constexpr int64_t kImgAlign = 256;
+
+// Is `st` being captured into a graph?  (The null stream cannot be.)
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return st && hipStreamIsCapturing(st, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
+}
 
 int64_t img_align(int64_t b) { return (b + kImgAlign - 1) / kImgAlign * kImgAlign; }
 
@@ -729,7 +736,12 @@ AR_EXPORT ar_status ar_plan_execute_noalloc(ar_plan* plan, void* const* bufs, vo
             ScratchImage* im = nullptr;  // its tables, whichever the records
             for (ScratchImage& h : sd.held)
                 if (h.serial == ex->serial && h.one == one) im = &h;
-            if (im && std::equal(im->bufs.begin(), im->bufs.end(), bufs, bufs + plan->n)) {
+            // Within a capture only what the last call used counts as there: other
+            // images may be replaced before the replays, which then need their
+            // own copy.
+            const bool last = sd.last == ex->serial;
+            if (im && std::equal(im->bufs.begin(), im->bufs.end(), bufs, bufs + plan->n) &&
+                (last || !capturing(st))) {
                 base = sd.ptr + im->off;
             } else {
                 const std::vector<void*> set(bufs, bufs + plan->n);
@@ -768,7 +780,8 @@ AR_EXPORT ar_status ar_plan_execute_noalloc(ar_plan* plan, void* const* bufs, vo
                 im = nullptr;  // (the route may have changed)
                 for (ScratchImage& h : sd.held)
                     if (h.serial == ex->serial && h.one == one) im = &h;
-                const int64_t from = im ? rec : 0;
+                const bool cap = capturing(st);
+                const int64_t from = im && !cap ? rec : 0;
                 // what was there is gone (unknown until the copy is enqueued)
                 sd.held.erase(std::remove_if(sd.held.begin(), sd.held.end(),
                                              [&](const ScratchImage& h) {
@@ -782,9 +795,11 @@ AR_EXPORT ar_status ar_plan_execute_noalloc(ar_plan* plan, void* const* bufs, vo
                 e = hipMemcpyAsync(sd.ptr + off + from, reinterpret_cast<const char*>(img.data()) + from,
                                    size_t(size - from), hipMemcpyHostToDevice, st);
                 if (e != hipSuccess) return fail(AR_ERR_HIP, hip_msg("scratch upload", e));
-                sd.held.push_back({ex->serial, one, set, off, size});
+                // (a captured copy has not run: the next call makes its own)
+                if (!cap) sd.held.push_back({ex->serial, one, set, off, size});
                 base = sd.ptr + off;
             }
+            sd.last = ex->serial;
         }
         if (one) {
             DevView v{};

@@ -197,6 +197,35 @@ def test_many_plans_share_the_no_allocation_array():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("N", [1024, 1027])
+def test_captured_copy_into_the_no_allocation_array(N):
+    # a call captured when another plan was the last one records its copy,
+    # which has not run when the next uncaptured call needs the tables
+    n = 4
+    xs0 = workloads.draw(n, N, "i32", "int1000", 5)
+    ref, got = to_device(xs0, "i32"), to_device(xs0, "i32")
+    s = torch.cuda.current_stream()
+    with arplan.Plan(n, N, "i32", "ring") as p, arplan.Plan(n, N, "i32", "cps") as q:
+        for r in (p, q):
+            r.execute_noalloc(got, s)
+            r.execute(ref, s)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        say("case: noalloc capture N=%d" % N)
+        with torch.cuda.graph(g):
+            p.execute_noalloc(got, torch.cuda.current_stream())
+        for rnd in range(3):
+            p.execute_noalloc(got, s)
+            p.execute(ref, s)
+            torch.cuda.synchronize()
+            g.replay()
+            p.execute(ref, s)
+            torch.cuda.synchronize()
+            for x, y in zip(to_host(got, "i32"), to_host(ref, "i32")):
+                assert np.array_equal(x, y), rnd
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "i32"])
 @pytest.mark.parametrize("n", [2, 3, 4, 5, 8, 12, 16])
 def test_phase_launches_on_element_aligned_buffers(n, dtype):
