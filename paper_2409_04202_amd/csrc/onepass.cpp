@@ -54,7 +54,10 @@ struct Values {
 };
 
 // Leaves of value v in computing order, appended to w; false when there are
-// more than n of them (a value used twice) or too many sums put aside.
+// more than n of them (a value used twice) or too many sums put aside.  `level`
+// counts the folds that v is an operand of: each brings a leaf besides v's, so
+// at n of them there are too many leaves, whatever lies below (which may be as
+// many folds as the plan has phases).
 struct Emit {
     const Values& vs;
     std::vector<uint32_t>& w;
@@ -62,7 +65,8 @@ struct Emit {
     bool rounds;       // step results are rounded (bf16)
     int32_t max_depth = 0;
 
-    bool run(int32_t v, int32_t depth) {
+    bool run(int32_t v, int32_t depth, size_t level = 0) {
+        if (level >= most) return false;
         max_depth = std::max(max_depth, depth);
         const Values::Val& x = vs.vals[size_t(v)];
         if (x.leaf >= 0) {
@@ -79,7 +83,8 @@ struct Emit {
             const bool is_fold = vs.vals[size_t(u)].leaf < 0;
             const size_t at = w.size();
             const bool aside = i > 0 && is_fold;
-            if (depth + int32_t(aside) > kOneMaxDepth || !run(u, depth + int32_t(aside))) return false;
+            if (depth + int32_t(aside) > kOneMaxDepth || !run(u, depth + int32_t(aside), level + 1))
+                return false;
             if (!is_fold) continue;
             if (aside) {
                 w[at] |= kOnePush;

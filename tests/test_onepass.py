@@ -7,6 +7,10 @@ the executed steps and walks the tiles of every kernel instance.  On the GPU,
 results equal the oracle's bit for bit at the sizes where the tiling changes.
 """
 
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -71,6 +75,25 @@ def test_plans_that_have_no_one_pass_form():
                 assert st == check.AR_OK, msg
         finally:
             check.ar_plan_destroy(h)
+
+
+@pytest.mark.parametrize("swap", [False, True])
+def test_a_long_chain_has_no_one_pass_form(swap):
+    # 300000 phases, each folding the one before: far more folds than buffers,
+    # found without descending them all (in a process of its own: a descent
+    # that deep runs out of stack)
+    code = """
+import sys
+sys.path.insert(0, %r)
+from checklib import arplan as check
+N, P, srcs = 1023, 300000, %r
+steps = [(q, "reduce", 0, srcs, 0, N) for q in range(P)] + [(P, "copy", 1, [0], 0, N)]
+h = check.ar_plan_create_custom(2, N, "f32", steps)
+print("launches", check.ar_plan_num_launches(h))
+""" % (os.path.dirname(os.path.abspath(__file__)), [1, 0] if swap else [0, 1])
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, (r.returncode, r.stderr[-500:])
+    assert int(r.stdout.split()[-1]) >= 300000, r.stdout
 
 
 # (kind, n, N, dtype, fan): every instance, with a partial last vector
