@@ -322,8 +322,7 @@ static void launch_dk(int align, int cm, int64_t blocks, hipStream_t st,
         blocks = (nunits + kcfg(K).WPB - 1) / kcfg(K).WPB;
     }
     const dim3 grid(static_cast<uint32_t>(blocks));
-    constexpr int kCachedU = K == 1 ? kNarrowU1 : 0;  // see kNarrowMinSrc
-    constexpr int kNarrowU = K == 0 ? kNarrowU0 : kCachedU;
+    constexpr int kNarrowU = K == 0 ? kNarrowU0 : K == 1 ? kNarrowU1 : 0;  // see kNarrowMinSrc
 #define AR_LAUNCH(V, C)                                                                \
     hipLaunchKernelGGL((phase_kernel<DT, K, V, C>), grid, block, 0, st, recs, stride, \
                        tiles, nunits, tps, te, rtg)
@@ -334,9 +333,7 @@ static void launch_dk(int align, int cm, int64_t blocks, hipStream_t st,
     else if (cm == 0 && narrow)
         hipLaunchKernelGGL((phase_kernel<DT, K, true, 0, kNarrowU>), grid, block, 0, st, recs,
                            stride, tiles, nunits, tps, te, rtg);
-    else if (cm == 0)
-        hipLaunchKernelGGL((phase_kernel<DT, K, true, 0, kCachedU>), grid, block, 0, st, recs,
-                           stride, tiles, nunits, tps, te, rtg);
+    else if (cm == 0) AR_LAUNCH(true, 0);
     else if (cm == 1) AR_LAUNCH(true, 1);
     else if (cm == 2) AR_LAUNCH(true, 2);
     else AR_LAUNCH(true, 3);

@@ -57,7 +57,12 @@ constexpr int64_t kWideBytes = int64_t(512) << 20;
 // 34.8 -> 35.1.
 // Folds of 6 sources lost (9.2 -> 9.5 at 2^16 fp32, 25.9 -> 27.9 at 2^22
 // bf16), and so did larger launches of either kind, which stream (RHD n = 8
-// over 2^26 1496 -> 1567, co-located PS n = 32 over 2^22 172 -> 205).
+// over 2^26 1496 -> 1567, co-located PS n = 32 over 2^22 172 -> 205), also with
+// cached loads and stores: wide and narrow, the 448 MiB copies of the (8, 8) tree
+// over 2^23 fp32 51.0 and 59.7 us a launch, of the (4, 8) tree 52.1 and 60.1; the
+// 12-source folds of the (8, 12) tree, 191 MiB over 2^21 fp32 39.0 and 42.9, over
+// 2^22 bf16 37.3 and 48.3 (112 to 255 MiB copies within 10 % of each other either
+// way).
 constexpr int kNarrowMinSrc = 8;
 // A runtime-source-count launch (a fan-in without an unrolled kernel)
 // moving less than kRtGroupMaxBytes keeps the loads of kRtGroup sources in
@@ -341,7 +346,7 @@ struct LaunchDesc {
     int32_t dsplit;          // waves per tile (split_tile), 1: one
     int32_t affinity;        // 1: the tile table places tiles by xcd_of
     int32_t wide;            // 1: the wide 2-source instance (kWideU per pass)
-    int32_t narrow;          // 1: the narrow runtime-k instance (kNarrowU0)
+    int32_t narrow;          // 1: the narrow copy or runtime-k instance (kNarrowU1, U0)
     int64_t bytes;           // (k + destinations) * len * e over the steps
     int64_t hbm;             // predicted HBM traffic: bytes, less the repeated
                              // reads of a range by the launch's copies

@@ -224,7 +224,8 @@ static void build_launches(const Plan& p, ExecState& ex) {
                 const int64_t keep = k >= 2 ? kKeepBytesFold : kKeepBytes;
                 if (written > keep || !next_reads_output) L.cm |= 2;
             }
-            L.narrow = L.kern_k == 0 && k >= kNarrowMinSrc && L.cm == 0;
+            L.narrow = bytes < kNtBytes &&
+                       (L.kern_k == 1 || (L.kern_k == 0 && k >= kNarrowMinSrc));
             L.wide = (L.kern_k == 2 && L.cm == 3 && bytes >= kWideBytes &&
                       maxdst < kSplitMinDst && te == int64_t(64) * kWideU * VEC &&
                       te == int64_t(cfg.TE) * VEC) ||

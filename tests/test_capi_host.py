@@ -539,11 +539,11 @@ def _launch_desc(handle, stage):
     f = arplan._lib.ar_debug_launch_desc
     f.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(ctypes.c_int64)]
     f.restype = ctypes.c_int32
-    out = (ctypes.c_int64 * 10)()
+    out = (ctypes.c_int64 * 11)()
     assert f(handle, stage, out) == arplan.AR_OK, arplan.ar_last_error()
     return {"k": out[0], "cm": out[1], "tile": out[2], "tiles": out[3], "wpb": out[4],
             "table": out[5], "group": out[6], "split": out[7], "affinity": out[8],
-            "wide": out[9]}
+            "wide": out[9], "narrow": out[10]}
 
 
 def test_full_size_forms_use_the_nontemporal_kernels():
@@ -670,6 +670,28 @@ def test_launch_kernels_by_form():
     with arplan.Plan(8, 1 << 12, "f32", "rhd") as p:
         with pytest.raises(arplan.ArError):
             arplan.ar_plan_launch_kernel(p.handle, len(p.launches()))
+
+
+@pytest.mark.parametrize("kind,n,N,dtype,fan,fuse", [
+    ("tree", 64, 1 << 23, "f32", (8, 8), 1), ("tree", 64, 1 << 23, "bf16", (8, 8), 0),
+    ("tree", 96, 96 * 21840, "f32", (8, 12), 1), ("tree", 96, 96 * 43680, "bf16", (8, 12), 1),
+    ("cps", 12, 1 << 18, "f32", None, 0), ("cps", 12, 1 << 22, "f32", None, 0),
+    ("cps", 6, 1 << 18, "f32", None, 0), ("rhd", 8, 1 << 20, "i32", None, 0)])
+def test_narrow_passes_only_below_64_mib(kind, n, N, dtype, fan, fuse):
+    # copies, and folds of 8 and more sources without an unrolled kernel, take
+    # few vectors a lane in launches of less than 64 MiB; larger ones do not,
+    # cached (cm 0) as they may be: the first four plans have such launches
+    with arplan.Plan(n, N, dtype, kind, fan) as p:
+        p.set_option(arplan.AR_OPT_FUSE, fuse)
+        p.set_option(arplan.AR_OPT_SLICE, 0)
+        L = p.launches()
+        d = [_launch_desc(p.handle, i) for i in range(len(L))]
+        for x, y in zip(L, d):
+            kinds = y["k"] == 1 or (y["k"] == 0 and x[1] >= 8)
+            assert y["narrow"] == int(kinds and x[4] < 64 << 20), (x, y)
+        if kind == "tree":
+            assert any(y["k"] in (0, 1) and y["cm"] == 0 and x[4] >= 64 << 20
+                       for x, y in zip(L, d)), (L, d)
 
 
 # 16-byte vectors per lane and source in one pass of each kernel (kcfg)
