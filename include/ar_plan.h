@@ -189,7 +189,9 @@ ar_status ar_plan_destroy(ar_plan* plan);
  * call is asynchronous and stream-ordered: it enqueues about one kernel
  * launch per phase (see ar_plan_num_launches) and returns; when the stream
  * reaches that point every buffer holds the AllReduce result, bit for bit
- * the result of running the steps phase by phase as listed.  The
+ * the result of running the steps phase by phase as listed (a NaN is a NaN:
+ * which of two NaN operands' sign and payload their sum keeps may differ from
+ * one launch form to another).  The
  * pointer array is read during the call only.  Any pointer alignment works;
  * buffers at their element's alignment may run as one one-pass launch
  * (AR_OPT_RESIDENT), otherwise 16-byte-aligned buffers take the vector path.

@@ -25,7 +25,10 @@ namespace arp {
 //               ends) and added to the one last put aside.
 // Every fold adds the same values in the same order as the plan's step and is
 // rounded where the step ends, so the bits are the plan's (a step of two
-// sources may have them swapped, which IEEE addition does not show).  A sum
+// sources may have them swapped, which shows in nothing but which payload two
+// NaNs leave; the compiler's operand order decides that in every launch form:
+// of 3726 positions with NaNs co-located PS n = 6 over 4099 fp32 gives another
+// than the first operand's in 2260 by its phase launches, in 2589 one-pass).  A sum
 // starts from -0.0 (0 for int32), which adding a value to leaves its bits.
 //
 // A wavefront owns 64 lanes x U vectors of LB bytes at one place of a
