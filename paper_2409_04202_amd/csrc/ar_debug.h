@@ -52,6 +52,11 @@ ar_status ar_debug_resident(ar_plan* plan, int32_t stage, int64_t* info,
  * for 11).
  * AR_ERR_INVALID_ARG for a sliced launch.  Host only. */
 ar_status ar_debug_launch_desc(ar_plan* plan, int32_t stage, int64_t* out);
+
+/* Let `plan` run one-pass where it would (on = 1, the default) or never (0):
+ * the launches that the one-pass form takes the place of then run.  Drops the
+ * plan's device state, like ar_plan_set_option.  Host only. */
+ar_status ar_debug_set_onepass(ar_plan* plan, int32_t on);
 #ifdef __cplusplus
 }
 #endif

@@ -841,3 +841,13 @@ AR_EXPORT ar_status ar_debug_launch_desc(ar_plan* plan, int32_t stage, int64_t* 
         return fail(AR_ERR_INTERNAL, e.what());
     }
 }
+
+AR_EXPORT ar_status ar_debug_set_onepass(ar_plan* plan, int32_t on) {
+    clear_error();
+    if (!plan || (on != 0 && on != 1)) return fail(AR_ERR_INVALID_ARG, "bad argument");
+    if (plan->onepass != on) {
+        exec_release(*plan);
+        plan->onepass = on;
+    }
+    return AR_OK;
+}

@@ -40,6 +40,7 @@ struct Plan {
     int32_t fuse = 1;   // AR_OPT_FUSE
     int32_t slice = 2;  // AR_OPT_SLICE: 0 never, 1 always (if possible), 2 auto
     int32_t resident = 1;  // AR_OPT_RESIDENT: sliced runs may keep their state in LDS
+    int32_t onepass = 1;   // 0: no one-pass launch (only the tests set it)
     ExecState* exec = nullptr;  // executor cache, built on first use
 
     int32_t num_phases() const {

@@ -577,6 +577,7 @@ ExecState* exec_state(Plan& p) {
                 return ex->one.ok ? onepass_time(p, ex->one)
                                   : std::numeric_limits<double>::infinity();
             };
+            const bool one_may = p.onepass != 0 && p.resident != 0 && p.n >= 2;
             bool one_stage = false;
             double t_whole = 0.0;  // predicted, of the runs chosen (AR_OPT_SLICE = 2)
             if (p.slice == 1 && P > 0) {
@@ -589,7 +590,6 @@ ExecState* exec_state(Plan& p) {
                 for (const PhaseCost& c : pc) t_phases += c.t_launch;
                 bool ragged = false;  // a step boundary off 16 bytes
                 for (const PhaseCost& c : pc) ragged = ragged || !c.aligned;
-                const bool one_may = p.resident != 0 && p.n >= 2;
                 ex->one_unaligned =
                     one_may && (p.n <= kOneFreeN || onepass_time(p, ex->one) < t_phases);
                 if (ragged && ex->one_unaligned)
@@ -628,7 +628,7 @@ ExecState* exec_state(Plan& p) {
                 // teams; over 2^12 8.2 us, by teams 6.5).  A streamed one
                 // runs its records one after the other and takes it when
                 // predicted faster (Ring n = 128 over 2^12 fp32 77 us, 7).
-                if (r.a == 0 && r.b == P && p.resident != 0 && p.n >= 2) {
+                if (r.a == 0 && r.b == P && one_may) {
                     const bool by_time = sd.streamed || (p.slice == 2 && onepass_teams(p));
                     const double t = sd.streamed ? stream_time(p, sd) : t_whole;
                     if (by_time)

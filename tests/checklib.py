@@ -11,6 +11,7 @@ handed to the hooks (``arplan._lib.ar_debug_*``).  The product library,
 sanitized host-only build) to bind instead.
 """
 
+import ctypes
 import importlib.util
 import os
 
@@ -33,3 +34,12 @@ def _load():
 
 
 arplan = _load()
+
+
+def set_onepass(handle, on):
+    """Let a plan of this library run one-pass (the default) or not: the
+    sliced, resident and streamed launches that the one-pass form takes the
+    place of then run."""
+    f = arplan._lib.ar_debug_set_onepass
+    f.argtypes, f.restype = [ctypes.c_void_p, ctypes.c_int32], ctypes.c_int32
+    assert f(handle, on) == arplan.AR_OK, arplan.ar_last_error()

@@ -40,7 +40,7 @@ def test_library_exports_every_declared_function():
     # the test build adds the hooks and nothing else
     extra = {f for f in _exported_functions(arplan.LIB_PATH) if f.startswith("ar_")} - declared
     assert extra == {"ar_debug_check_tiling", "ar_debug_exec_steps", "ar_debug_resident",
-                     "ar_debug_launch_desc"}
+                     "ar_debug_launch_desc", "ar_debug_set_onepass"}
 
 
 def _exported_functions(path):

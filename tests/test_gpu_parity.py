@@ -14,6 +14,7 @@ import torch
 import oracle
 from paper_2409_04202_amd import workloads
 
+from checklib import arplan as check, set_onepass
 from gpu_helpers import run_plan, say, to_device, to_host
 
 pytestmark = pytest.mark.gpu
@@ -28,27 +29,39 @@ def _oracle_plan(kind, n, N, fan):
     return oracle.make_plan(kind, n, N, fan)
 
 
+def _plan(onepass, *a):
+    """A plan that may run one-pass, or (of the test build, the same code) one
+    that never does: its sliced, resident and streamed launches run then."""
+    p = (arplan if onepass else check).Plan(*a)
+    if not onepass:
+        set_onepass(p.handle, 0)
+    return p
+
+
 def _full_compare(kind, n, N, dtype, fan=None, dist="uniform", seed=1,
                   pad=0, xs0=None, fuse=1, slice_=2, resident=1):
+    # with the options that allow a one-pass launch, without it as well
     say("case: %s n=%d N=%d %s fan=%s pad=%d fuse=%d slice=%d resident=%d" % (
         kind, n, N, dtype, fan if kind != "gentree" else len(fan), pad, fuse, slice_,
         resident))
     if xs0 is None:
         xs0 = workloads.draw(n, N, dtype, dist, seed)
     ref = oracle.execute(_oracle_plan(kind, n, N, fan), [x.copy() for x in xs0], dtype)
-    ts = to_device(xs0, dtype, pad)
-    with arplan.Plan(n, N, dtype, kind, fan) as p:
-        p.set_option(arplan.AR_OPT_FUSE, fuse)
-        p.set_option(arplan.AR_OPT_SLICE, slice_)
-        p.set_option(arplan.AR_OPT_RESIDENT, resident)
-        run_plan(p, ts)
-    got = to_host(ts, dtype)
-    for q in range(n):
-        if not np.array_equal(got[q], ref[q]):
-            bad = np.nonzero(got[q] != ref[q])[0]
-            raise AssertionError("%s n=%d N=%d %s: processor %d differs at %d "
-                                 "positions, first %s" % (kind, n, N, dtype, q,
-                                                          len(bad), bad[:8]))
+    for onepass in ((1, 0) if slice_ and resident else (1,)):
+        ts = to_device(xs0, dtype, pad)
+        with _plan(onepass, n, N, dtype, kind, fan) as p:
+            p.set_option(arplan.AR_OPT_FUSE, fuse)
+            p.set_option(arplan.AR_OPT_SLICE, slice_)
+            p.set_option(arplan.AR_OPT_RESIDENT, resident)
+            run_plan(p, ts)
+        got = to_host(ts, dtype)
+        del ts
+        for q in range(n):
+            if not np.array_equal(got[q], ref[q]):
+                bad = np.nonzero(got[q] != ref[q])[0]
+                raise AssertionError("%s n=%d N=%d %s onepass=%d: processor %d differs at %d "
+                                     "positions, first %s" % (kind, n, N, dtype, onepass, q,
+                                                              len(bad), bad[:8]))
     return got, xs0
 
 
@@ -126,7 +139,7 @@ def test_sliced_runs_between_phase_launches():
     # first three run bit-exact
     mixed = []
     for kind, n, N, dtype, fan in _MIXED_CANDIDATES:
-        with arplan.Plan(n, N, dtype, kind, fan) as p:
+        with _plan(0, n, N, dtype, kind, fan) as p:
             ph = [x[0] for x in p.launches()]
         if any(x < 0 for x in ph) and any(x >= 0 for x in ph):
             mixed.append((kind, n, N, dtype, fan))
@@ -141,10 +154,11 @@ def test_sliced_runs_between_phase_launches():
     ("ring", 128, 1 << 12, "f32", "stream_kernel"), ("ring", 256, 1 << 15, "f32", "stream_kernel"),
     ("ring", 128, 1 << 18, "bf16", "stream_kernel"), ("rhd", 128, 1 << 12, "f32", "split_kernel")])
 def test_automatic_choice_beyond_64_buffers(kind, n, N, dtype, kernel):
-    # the automatic choice for more than 64 buffers: Ring as one streamed
-    # launch, RHD's short 128-destination phase as a split launch
-    # (tests/test_capi_host.py pins the choices); every element vs the oracle
-    with arplan.Plan(n, N, dtype, kind) as p:
+    # the automatic choice for more than 64 buffers where it is not one-pass:
+    # Ring as one streamed launch, RHD's short 128-destination phase as a split
+    # launch (tests/test_capi_host.py pins the choices); every element vs the
+    # oracle
+    with _plan(0, n, N, dtype, kind) as p:
         assert kernel in p.launch_kernels()
     got, xs0 = _full_compare(kind, n, N, dtype, None, "uniform", seed=n + 5)
     if dtype == "bf16":
@@ -157,10 +171,12 @@ def test_automatic_choice_beyond_64_buffers(kind, n, N, dtype, kernel):
 
 # ------------------------------------------- full size, every element
 
-# The executor forms the benchmark times: the default choice, phase launches
-# with the rewrites, and the plan as written (every step as listed, one
-# launch per phase).  (AR_OPT_FUSE, AR_OPT_SLICE, AR_OPT_RESIDENT)
-BENCH_FORMS = [("default", 1, 2, 1), ("phase launches", 1, 0, 1), ("as written", 0, 0, 1)]
+# The executor forms the benchmark times: the default choice (with and without
+# the one-pass launch), phase launches with the rewrites, and the plan as
+# written (every step as listed, one launch per phase).
+# (AR_OPT_FUSE, AR_OPT_SLICE, AR_OPT_RESIDENT, one-pass)
+BENCH_FORMS = [("default", 1, 2, 1, 1), ("default, not one-pass", 1, 2, 1, 0),
+               ("phase launches", 1, 0, 1, 1), ("as written", 0, 0, 1, 1)]
 
 
 def _full_size_every_element(name, forms):
@@ -174,11 +190,11 @@ def _full_size_every_element(name, forms):
     ref = oracle.execute(_oracle_plan(c["kind"], n, N, c["fanin"]),
                          [x.copy() for x in xs0], dt)
     pristine = to_device(xs0, dt)
-    for label, fuse, slice_, resident in forms:
-        say("case: full-size %s, %s (fuse=%d slice=%d resident=%d)" % (
-            name, label, fuse, slice_, resident))
+    for label, fuse, slice_, resident, onepass in forms:
+        say("case: full-size %s, %s (fuse=%d slice=%d resident=%d onepass=%d)" % (
+            name, label, fuse, slice_, resident, onepass))
         ts = [t.clone() for t in pristine]
-        with arplan.Plan(n, N, dt, c["kind"], c["fanin"]) as p:
+        with _plan(onepass, n, N, dt, c["kind"], c["fanin"]) as p:
             p.set_option(arplan.AR_OPT_FUSE, fuse)
             p.set_option(arplan.AR_OPT_SLICE, slice_)
             p.set_option(arplan.AR_OPT_RESIDENT, resident)
@@ -213,8 +229,8 @@ def test_large_resident_with_partial_tiles(N):
     # RHD n = 8 as one resident launch whose segments end in a partial tile
     # (N / 8 is not a multiple of 256 elements); at 2^24 + 160 the run moves
     # more than the last-level cache and streams its rows nontemporally
-    with arplan.Plan(8, N, "f32", "rhd") as p:
-        if N > 1 << 24:  # the default choice at this size
+    with _plan(0, 8, N, "f32", "rhd") as p:
+        if N > 1 << 24:  # the default choice at this size, where not one-pass
             assert [x[0] for x in p.launches()] == [-2]
         p.set_option(arplan.AR_OPT_SLICE, 1)
         L = p.launches()
@@ -227,7 +243,7 @@ def test_large_resident_nontemporal_dtypes(dtype, N):
     # RHD n = 8 as one resident launch moving more than the last-level cache
     # (nontemporal rows) in bf16 and int32, every element
     n = 8
-    with arplan.Plan(n, N, dtype, "rhd") as p:
+    with _plan(0, n, N, dtype, "rhd") as p:
         L = p.launches()
         assert [x[0] for x in L] == [-2] and L[0][4] > 512 << 20
     _full_compare("rhd", n, N, dtype, None, "int1000" if dtype == "i32" else "uniform",
@@ -251,7 +267,7 @@ STREAMED = [("tree", 512, 1 << 15, "bf16", (8, 8, 8)), ("tree", 512, 1 << 16, "f
 def test_streamed_whole_plan(kind, n, N, dtype, fan, fuse):
     # the whole plan as one streamed launch (LDS slots shared by values,
     # loads ahead, stores as soon as a final value is there), bit-exact
-    with arplan.Plan(n, N, dtype, kind, fan) as p:
+    with _plan(0, n, N, dtype, kind, fan) as p:
         p.set_option(arplan.AR_OPT_FUSE, fuse)
         p.set_option(arplan.AR_OPT_SLICE, 1)
         assert [x[0] for x in p.launches()] == [-3]
@@ -331,10 +347,10 @@ def test_streamed_full_size(name):
     # the full-size workloads with more than 64 buffers as one streamed
     # launch, every element
     c = workloads.CONFIGS[name]
-    with arplan.Plan(c["n"], c["N"], c["dtype"], c["kind"], c["fanin"]) as p:
+    with _plan(0, c["n"], c["N"], c["dtype"], c["kind"], c["fanin"]) as p:
         p.set_option(arplan.AR_OPT_SLICE, 1)
         assert [x[0] for x in p.launches()] == [-3]
-    _full_size_every_element(name, [("whole plan streamed", 1, 1, 1)])
+    _full_size_every_element(name, [("whole plan streamed", 1, 1, 1, 0)])
 
 
 # --------------------------------------------------------------- edge cases
@@ -740,13 +756,14 @@ def test_runs_on_a_side_stream_in_order():
         assert np.array_equal(outs[q].numpy(), ref[q]), q
 
 
-@pytest.mark.parametrize("kind,n,N,fan,slice_,resident", [
-    ("ring", 8, 8 * 1024, None, 1, 1),           # one resident launch
-    ("ring", 8, 8 * 1024, None, 1, 0),           # one plain sliced launch
-    ("rhd", 8, 1 << 20, None, 0, 1),             # phase launches
-    ("tree", 64, 64 * 256, (8, 8), 2, 1),        # the default choice
-    ("ring", 128, 128 * 32, None, 2, 1)])        # the default choice: streamed
-def test_graph_capture_replays(kind, n, N, fan, slice_, resident):
+@pytest.mark.parametrize("kind,n,N,fan,slice_,resident,onepass", [
+    ("ring", 8, 8 * 1024, None, 1, 1, 0),        # one resident launch
+    ("ring", 8, 8 * 1024, None, 1, 0, 1),        # one plain sliced launch
+    ("rhd", 8, 1 << 20, None, 0, 1, 1),          # phase launches
+    ("tree", 64, 64 * 256, (8, 8), 2, 1, 1),     # the default choice
+    ("ring", 128, 128 * 32, None, 2, 1, 1),      # the default choice: one-pass
+    ("ring", 128, 128 * 32, None, 2, 1, 0)])     # and without it: streamed
+def test_graph_capture_replays(kind, n, N, fan, slice_, resident, onepass):
     # an execution captured in a HIP graph after a first eager execution (which
     # uploads the step records, so that capture records kernel launches only)
     # replays the same work: every replay, with eager work and a
@@ -754,9 +771,10 @@ def test_graph_capture_replays(kind, n, N, fan, slice_, resident):
     xs0 = workloads.draw(n, N, "i32", "int1000", 21)
     plan_o = _oracle_plan(kind, n, N, fan)
     want = oracle.execute(plan_o, [x.copy() for x in xs0], "i32")
-    say("case: graph capture %s n=%d N=%d slice=%d resident=%d" % (kind, n, N, slice_, resident))
+    say("case: graph capture %s n=%d N=%d slice=%d resident=%d onepass=%d" % (
+        kind, n, N, slice_, resident, onepass))
     ts = to_device(xs0, "i32")
-    with arplan.Plan(n, N, "i32", kind, fan) as p:
+    with _plan(onepass, n, N, "i32", kind, fan) as p:
         p.set_option(arplan.AR_OPT_SLICE, slice_)
         p.set_option(arplan.AR_OPT_RESIDENT, resident)
         run_plan(p, ts)
@@ -787,9 +805,9 @@ def test_whole_plan_launch_with_timer_and_repeats(resident):
     ref = oracle.execute(plan_o, [x.copy() for x in xs0], "f32")
     ref2 = oracle.execute(plan_o, [x.copy() for x in ref], "f32")
     ts = to_device(xs0, "f32")
-    t = arplan.ar_timer_create(8)
+    t = check.ar_timer_create(8)
     try:
-        with arplan.Plan(n, N, "f32", "ring") as p:
+        with _plan(0, n, N, "f32", "ring") as p:
             p.set_option(arplan.AR_OPT_SLICE, 1)
             p.set_option(arplan.AR_OPT_RESIDENT, resident)
             (ph, k, d, cnt, b), = p.launches()
@@ -802,10 +820,10 @@ def test_whole_plan_launch_with_timer_and_repeats(resident):
             torch.cuda.synchronize()
             got = to_host(ts, "f32")
             assert all(np.array_equal(got[q], ref2[q]) for q in range(n))
-            recs = arplan.ar_timer_read(t, 8)
+            recs = check.ar_timer_read(t, 8)
             assert [li for li, _ in recs] == [0, 0] and all(ms > 0 for _, ms in recs)
     finally:
-        arplan.ar_timer_destroy(t)
+        check.ar_timer_destroy(t)
 
 
 GENTREES = [[3, 0, 0, 2, 0, 0], [2, 0, 2, 0, 2, 0, 0],
@@ -911,20 +929,21 @@ def test_wide_eight_source_launches(dtype):
     torch.cuda.empty_cache()
 
 
+# (AR_OPT_FUSE, AR_OPT_SLICE, AR_OPT_RESIDENT, one-pass)
 @pytest.mark.parametrize("N,forms", [
-    ((1 << 30) + 4099, [(1, 2, 1), (0, 0, 1)]),     # unaligned steps: phase launches
-    ((1 << 30) + 8192, [(1, 1, 1), (0, 0, 1)])])    # aligned: one resident launch
+    ((1 << 30) + 4099, [(1, 2, 1, 1), (0, 0, 1, 1)]),   # unaligned steps: one-pass, phases
+    ((1 << 30) + 8192, [(1, 1, 1, 0), (0, 0, 1, 1)])])  # aligned: one resident launch, phases
 def test_buffers_larger_than_4_GiB(N, forms):
-    # every byte offset past 2^32: 64-bit addressing in the phase kernel (with
-    # element-wise heads and tails) and the resident kernel, every element
-    # compared with the oracle
+    # every byte offset past 2^32: 64-bit addressing in the one-pass kernel, the
+    # phase kernel (with element-wise heads and tails) and the resident kernel,
+    # every element compared with the oracle
     n = 2
     say("case: rhd n=2 N=%d (4 GiB + per buffer)" % N)
     xs0 = workloads.draw(n, N, "f32", "uniform", 77)
     ref = oracle.execute(oracle.rhd(n, N), [x.copy() for x in xs0], "f32")
     del xs0[1:]
-    for fuse, slice_, resident in forms:
-        with arplan.Plan(n, N, "f32", "rhd") as p:
+    for fuse, slice_, resident, onepass in forms:
+        with _plan(onepass, n, N, "f32", "rhd") as p:
             p.set_option(arplan.AR_OPT_FUSE, fuse)
             p.set_option(arplan.AR_OPT_SLICE, slice_)
             kinds = [x[0] for x in p.launches()]
@@ -932,7 +951,7 @@ def test_buffers_larger_than_4_GiB(N, forms):
                 assert kinds == [-2]
             ts = [torch.from_numpy(x).to("cuda") for x in
                   workloads.draw(n, N, "f32", "uniform", 77)]
-            say("  fuse=%d slice=%d launches %s" % (fuse, slice_, kinds))
+            say("  fuse=%d slice=%d onepass=%d launches %s" % (fuse, slice_, onepass, kinds))
             run_plan(p, ts)
         for q in range(n):
             g = ts[q].cpu().numpy()

@@ -21,7 +21,7 @@ from oracle.execute import fold
 from oracle.plans import Plan as OPlan, Step as OStep
 
 from paper_2409_04202_amd import workloads
-from checklib import arplan
+from checklib import arplan, set_onepass
 
 from test_capi_host import _check_tiling
 from test_exec_rewrites_host import _random_plan
@@ -204,6 +204,7 @@ def _interpret(tables, bufs, dtype):
 
 
 def _check_whole_plan(handle, ref_plan, n, N, dtype, seed):
+    set_onepass(handle, 0)
     arplan.ar_plan_set_option(handle, arplan.AR_OPT_SLICE, 1)
     assert arplan.ar_plan_num_launches(handle) == 1
     kind = arplan.ar_plan_launch_info(handle, 0)[0]
@@ -247,16 +248,19 @@ def test_whole_plan_resident_program(kind, n, fan, dtype, fuse):
 def test_more_than_64_buffers_run_streamed():
     # a row per buffer up to 64 buffers; beyond, LDS slots shared by values
     with arplan.Plan(128, 128 * 4, "f32", "ring") as p:
+        set_onepass(p.handle, 0)
         p.set_option(arplan.AR_OPT_SLICE, 1)
         L = p.launches()
         assert len(L) == 1 and L[0][0] == -3
         assert _resident_tables(p.handle, 0) is not None and 0 < _resident_tables.slots <= 64
     with arplan.Plan(64, 64 * 4, "f32", "ring") as p:
+        set_onepass(p.handle, 0)
         p.set_option(arplan.AR_OPT_SLICE, 1)
         assert p.launches()[0][0] == -2
         assert _resident_tables(p.handle, 0) is not None and _resident_tables.slots == 0
     # a 100-source fold needs more than 64 slots at once: plain sliced
     with arplan.Plan(100, 100 * 4, "f32", "cps") as p:
+        set_onepass(p.handle, 0)
         p.set_option(arplan.AR_OPT_SLICE, 1)
         assert p.launches()[0][0] == -1 and _resident_tables(p.handle, 0) is None
 
@@ -299,11 +303,13 @@ def test_random_custom_plans_resident_program(seed):
 
 @pytest.mark.parametrize("name", ["sweep_ring_n64_f32_N4096", "sweep_ring_n64_bf16_N4096"])
 def test_workload_runs_resident_by_default(name):
-    # the small-message workloads run as one resident launch by default; the
-    # program is checked at a reduced N with the same block structure
+    # the small-message workloads run as one resident launch by default where
+    # not one-pass; the program is checked at a reduced N with the same block
+    # structure
     c = workloads.CONFIGS[name]
     n = c["n"]
     with arplan.Plan(n, c["N"], c["dtype"], c["kind"], c.get("fanin")) as p:
+        set_onepass(p.handle, 0)
         L = p.launches()
         assert len(L) == 1 and L[0][0] == -2, L
     N = n * 4 * 5
@@ -320,6 +326,7 @@ def test_ring_program_is_one_chain_and_a_broadcast():
     # (alias table)
     n, N = 64, 64 * 64 * 4
     with arplan.Plan(n, N, "f32", "ring") as p:
+        set_onepass(p.handle, 0)
         p.set_option(arplan.AR_OPT_SLICE, 1)
         units, prog = _resident_tables(p.handle, 0)
         for lo, load, store, nv, off, nw, alias in units:

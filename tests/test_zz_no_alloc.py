@@ -12,6 +12,7 @@ import torch
 import oracle
 from paper_2409_04202_amd import workloads
 
+from checklib import arplan as check, set_onepass
 from gpu_helpers import say, to_device, to_host
 
 pytestmark = pytest.mark.gpu
@@ -95,7 +96,9 @@ def test_repeats_new_buffers_and_alternating_plans():
     ("tree", 64, 1 << 16, "f32", (8, 8), 1, "sliced_kernel")])
 def test_every_launch_kind(kind, n, N, dtype, fan, slice_, kernel):
     xs0, ref, got = _case(kind, n, N, dtype, fan, seed=n)
-    with arplan.Plan(n, N, dtype, kind, fan) as p:
+    # (of the test build, so that the launches a one-pass one takes the place of run)
+    with check.Plan(n, N, dtype, kind, fan) as p:
+        set_onepass(p.handle, 0)
         p.set_option(arplan.AR_OPT_SLICE, slice_)
         p.set_option(arplan.AR_OPT_RESIDENT, 0 if kernel == "sliced_kernel" else 1)
         assert kernel in p.launch_kernels(), p.launch_kernels()
