@@ -14,7 +14,7 @@ region.
 
 Every workload is timed in two forms:
 
-  default     the executor's own choice (rewrites, sliced or resident runs);
+  default     the executor's own choice (rewrites; sliced, resident or one-pass runs);
               its time is the AllReduce's algorithm bandwidth n * N * e / t
   as_written  every plan step as listed, one launch per phase
               (AR_OPT_FUSE = 0, AR_OPT_SLICE = 0): each launch moves exactly
@@ -29,8 +29,8 @@ Prints one JSON line.  The headline (RHD, n = 8, N = 2^26 fp32):
               phases): their algorithmic bytes over their HIP-event time,
               against MI355X's 8 TB/s HBM peak
   executor_roofline  the default form's launches that reduce, on the
-              bytes they move (a resident launch moves each buffer tile
-              once in and once out: 2 * n * N * e)
+              bytes they move (a resident or one-pass launch moves each
+              buffer tile once in and once out: 2 * n * N * e)
   cpu_baseline  the CPU oracle executing the same plan on the host
   configs     every workload (each config of the scope, the GenTree
               topologies and the n = 64 sweep) in both forms, each with a
@@ -56,7 +56,6 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# kernel of a launch by its phase field in ar_plan_launch_info
 HEADLINE = "rhd_n8_f32"
 FORMS = {"default": {}, "as_written": {"fuse": 0, "slice": 0}}
 
@@ -451,7 +450,7 @@ def headline_line(h, K, W, name):
         "kernel": " + ".join(dk),
         "form": "default executor: its launches that reduce",
         "bytes": ("rows loaded and stored, each buffer tile once: 2 * n * N * e"
-                  if dk == ["resident_kernel"] else "(k + d) * len * e per executed step"),
+                  if dk in (["resident_kernel"], ["onepass_kernel"]) else "(k + d) * len * e per executed step"),
         "launches_per_step": d["reduce_launches"],
         "bytes_per_launch": round(d["reduce_bytes"] / max(1, d["reduce_launches"])),
         "ms_per_launch": round(d["reduce_ms"] / max(1, d["reduce_launches"])

@@ -314,15 +314,14 @@ ar_status ar_plan_set_option(ar_plan* plan, int32_t option, int64_t value);
 /* The kernel launches one execution on 16-byte aligned buffers issues (host
  * only, no GPU call): their number, and for launch i the plan phase its
  * steps come from (-1 for a sliced launch, -2 for a resident one, -3 for a
- * streamed resident one; a one-pass launch counts as resident, or as the
- * whole-plan launch whose form it is), their
+ * streamed resident one, -4 for a one-pass one), their
  * source count (the
- * largest, for a sliced launch), the most destinations any of its
+ * largest, for a launch of several phases), the most destinations any of its
  * steps stores to, its number of steps and its algorithmic bytes:
  * (k + destinations) * len * e summed over its steps (each source read
- * once, each destination written once); for a resident launch, the bytes
- * of the buffer tiles it loads and stores (each once; a whole AllReduce
- * run resident moves 2 * n * N * e).  Any out-pointer may be NULL. */
+ * once, each destination written once); for a resident or one-pass launch,
+ * the bytes of the buffer tiles it loads and stores (each once; a whole
+ * AllReduce run so moves 2 * n * N * e).  Any out-pointer may be NULL. */
 ar_status ar_plan_num_launches(const ar_plan* plan, int32_t* count);
 ar_status ar_plan_launch_info(const ar_plan* plan, int32_t i, int32_t* phase,
                               int32_t* nsrc, int32_t* max_dst,
@@ -333,13 +332,14 @@ ar_status ar_plan_launch_info(const ar_plan* plan, int32_t i, int32_t* phase,
  * AR_KERNEL_SPLIT, a workgroup per wave tile, each wavefront storing the
  * folded tile to a share of the step's destinations (a launch of few tiles
  * whose steps store to many buffers; on unaligned buffers it runs as
- * AR_KERNEL_PHASE); AR_KERNEL_SLICED, AR_KERNEL_RESIDENT and AR_KERNEL_STREAM
- * for the sliced, resident and streamed resident launches (phase -1, -2 and
- * -3 above).  Host only, no GPU call.  AR_ERR_INVALID_ARG for a NULL plan or
+ * AR_KERNEL_PHASE); AR_KERNEL_SLICED, AR_KERNEL_RESIDENT, AR_KERNEL_STREAM
+ * and AR_KERNEL_ONEPASS for the sliced, resident, streamed resident and
+ * one-pass launches (phase -1, -2, -3 and -4 above; a one-pass launch of a
+ * short plan over many buffers takes a workgroup per tile).  Host only, no GPU call.  AR_ERR_INVALID_ARG for a NULL plan or
  * kernel, or i out of range. */
 typedef enum ar_kernel {
     AR_KERNEL_PHASE = 0, AR_KERNEL_SPLIT = 1, AR_KERNEL_SLICED = 2,
-    AR_KERNEL_RESIDENT = 3, AR_KERNEL_STREAM = 4
+    AR_KERNEL_RESIDENT = 3, AR_KERNEL_STREAM = 4, AR_KERNEL_ONEPASS = 5
 } ar_kernel;
 ar_status ar_plan_launch_kernel(const ar_plan* plan, int32_t i, int32_t* kernel);
 

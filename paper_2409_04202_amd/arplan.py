@@ -295,7 +295,7 @@ def ar_plan_launch_info(plan, i):
 
 
 KERNEL_NAMES = {0: "phase_kernel", 1: "split_kernel", 2: "sliced_kernel",
-                3: "resident_kernel", 4: "stream_kernel"}
+                3: "resident_kernel", 4: "stream_kernel", 5: "onepass_kernel"}
 
 
 def ar_plan_launch_kernel(plan, i):
@@ -443,7 +443,7 @@ class Plan:
     def launches(self):
         """[(phase, nsrc, max_dst, num_steps, bytes)] per kernel launch; phase
         is the plan phase of a phase launch, -1 for a sliced launch, -2 for a
-        resident one and -3 for a streamed resident one."""
+        resident one, -3 for a streamed resident one and -4 for a one-pass one."""
         return [ar_plan_launch_info(self.handle, i)
                 for i in range(ar_plan_num_launches(self.handle))]
 

@@ -959,7 +959,7 @@ AR_EXPORT ar_status ar_plan_launch_kernel(const ar_plan* plan, int32_t i, int32_
             *kernel = sd.streamed ? AR_KERNEL_STREAM : sd.resident ? AR_KERNEL_RESIDENT
                                                                    : AR_KERNEL_SLICED;
         } else if (stg.launch < 0) {
-            *kernel = AR_KERNEL_RESIDENT;
+            *kernel = AR_KERNEL_ONEPASS;
         } else {
             *kernel = ex->launches[size_t(stg.launch)].dsplit > 1 ? AR_KERNEL_SPLIT
                                                                    : AR_KERNEL_PHASE;
@@ -992,7 +992,7 @@ AR_EXPORT ar_status ar_plan_launch_info(const ar_plan* plan, int32_t i, int32_t*
             return AR_OK;
         }
         if (stg.launch < 0) {  // the one-pass launch
-            if (phase) *phase = -2;
+            if (phase) *phase = -4;
             if (nsrc) *nsrc = ex->one.max_k;
             if (max_dst) *max_dst = ex->one.max_dst;
             if (num_steps) *num_steps = ex->one.nsteps;

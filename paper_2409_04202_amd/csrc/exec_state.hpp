@@ -478,9 +478,7 @@ struct ExecState {
     std::vector<Stage> stages;   // the launches for 16-byte aligned buffers
     std::vector<Stage> run_stages;  // the same without the one-pass launch
     OnePlan one;
-    bool one_aligned = false;    // 16-byte aligned buffers run one.  `stages`
-                                 // is then that launch, or the resident or
-                                 // streamed slice whose form it takes
+    bool one_aligned = false;    // 16-byte aligned buffers run one
     bool one_unaligned = false;  // others may (each at its element's alignment),
                                  // when there is a one-pass form
     std::vector<DevState*> dev;  // indexed by device ordinal

@@ -670,11 +670,8 @@ ExecState* exec_state(Plan& p) {
                     last = sl;
                 }
             }
-            ex->stages = ex->run_stages;
-            if (one_stage) {
-                ex->stages.assign(1, Stage{-1, -1});
-                ex->one_aligned = true;
-            }
+            ex->one_aligned = ex->one_aligned || one_stage;
+            ex->stages = ex->one_aligned ? std::vector<Stage>(1, Stage{-1, -1}) : ex->run_stages;
         } catch (...) {
             delete ex;
             throw;

@@ -21,7 +21,7 @@ product = pytest.importorskip(
     reason="HIP library not built (run python -m paper_2409_04202_amd.build)")
 # everything below the export test runs on the test build (same code, plus
 # the checking hooks)
-from checklib import arplan  # noqa: E402
+from checklib import arplan, set_onepass  # noqa: E402
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "ar_plan.h")
@@ -371,6 +371,7 @@ def test_whole_plan_launch_schedule(kind, n, N, fan, dtype):
     # aligned; the host check walks its tiles and compares the schedule with
     # the steps of every phase
     with arplan.Plan(n, N, dtype, kind, fan) as p:
+        set_onepass(p.handle, 0)
         p.set_option(arplan.AR_OPT_SLICE, 1)
         off = oracle.block_bounds(N, n)
         vec = 16 // (4 if dtype == "f32" else 2)
@@ -399,6 +400,11 @@ def test_whole_plan_launch_schedule(kind, n, N, fan, dtype):
             # stored once
             esize = 4 if dtype == "f32" else 2
             assert b2 == 2 * n * N * esize
+            # ... and so does the one-pass launch, where it takes its place
+            set_onepass(p.handle, 1)
+            (ph, k1, d1, cnt1, b1), = p.launches()
+            assert ph in (marker, -4) and (k1, cnt1, b1) == (k, cnt, b2)
+            set_onepass(p.handle, 0)
             p.set_option(arplan.AR_OPT_SLICE, 0)
             assert b == sum(x[4] for x in p.launches())
 
@@ -489,25 +495,29 @@ def test_gentree_errors():
         E.ar_plan_destroy(h)
 
 
+@pytest.mark.parametrize("onepass", [0, 1])
 @pytest.mark.parametrize("name", sorted(__import__(
     "paper_2409_04202_amd.workloads", fromlist=["CONFIGS"]).CONFIGS))
-def test_sliced_runs_of_workloads(name):
+def test_sliced_runs_of_workloads(name, onepass):
     # AR_OPT_SLICE = 2 partitions the executed phases into sliced runs and
     # phase launches: the same executed steps (same bytes) as the phase
     # launches, every launch tiled exactly; the 2 GiB RHD plan, whose
-    # phases each write more than the 256 MiB cache, runs resident or as
-    # phase launches, never plain sliced
+    # phases each write more than the 256 MiB cache, runs resident, one-pass
+    # or as phase launches, never plain sliced
     from paper_2409_04202_amd import workloads
     c = workloads.CONFIGS[name]
     esize = 2 if c["dtype"] == "bf16" else 4
     with arplan.Plan(c["n"], c["N"], c["dtype"], c["kind"], c["fanin"]) as p:
+        set_onepass(p.handle, onepass)
         L = p.launches()
         p.set_option(arplan.AR_OPT_SLICE, 0)
         L0 = p.launches()
         assert sum(x[3] for x in L) == sum(x[3] for x in L0)
         # a resident launch moves each buffer position of its run at most
-        # once in and once out; the plain forms move the steps' bytes
+        # once in and once out, a one-pass launch all of them; the plain forms
+        # move the steps' bytes
         assert all(x[4] <= 2 * c["n"] * c["N"] * esize for x in L if x[0] == -2)
+        assert all(x[4] == 2 * c["n"] * c["N"] * esize for x in L if x[0] == -4)
         p.set_option(arplan.AR_OPT_RESIDENT, 0)
         p.set_option(arplan.AR_OPT_SLICE, 2)
         assert sum(x[4] for x in p.launches()) == sum(x[4] for x in L0)
@@ -522,7 +532,8 @@ def test_sliced_runs_of_workloads(name):
             assert st == arplan.AR_OK, msg
         if name == "rhd_n8_f32":
             # each buffer in and out once: 4 GiB against 7.5 GiB of phases
-            assert [(x[0], x[4]) for x in L] == [(-2, 2 * c["n"] * c["N"] * esize)]
+            assert [(x[0], x[4]) for x in L] == [(-4 if onepass else -2,
+                                                  2 * c["n"] * c["N"] * esize)]
             p.set_option(arplan.AR_OPT_RESIDENT, 0)
             assert all(x[0] >= 0 for x in p.launches())
             p.set_option(arplan.AR_OPT_RESIDENT, 1)
@@ -531,8 +542,8 @@ def test_sliced_runs_of_workloads(name):
             # a chain far too long for a sliced launch
             assert L[-1][0] == 5
         if name.startswith("sweep_ring"):
-            # 126 phases of short steps: one sliced launch
-            assert len(L) == 1 and L[0][0] in (-1, -2)
+            # 126 phases of short steps: one launch
+            assert len(L) == 1 and L[0][0] in (-1, -2, -4)
 
 
 def _launch_desc(handle, stage):
@@ -655,7 +666,7 @@ def test_split_launches(kind, n, N, fan, dtype, k, cm):
 def test_launch_kernels_by_form():
     # the kernel each launch of the benchmark's workloads runs, default form
     from paper_2409_04202_amd import workloads
-    expect = {"rhd_n8_f32": ["resident_kernel"],
+    expect = {"rhd_n8_f32": ["onepass_kernel"],
               "tree8x8x8_n512_bf16": ["phase_kernel", "phase_kernel", "split_kernel",
                                       "phase_kernel"],
               "tree8x8_n64_f32": ["phase_kernel", "sliced_kernel", "phase_kernel"]}
@@ -663,10 +674,15 @@ def test_launch_kernels_by_form():
         c = workloads.CONFIGS[name]
         with arplan.Plan(c["n"], c["N"], c["dtype"], c["kind"], c["fanin"]) as p:
             assert p.launch_kernels() == kernels, (name, p.launch_kernels())
-    # n > 64 with AR_OPT_SLICE = 1: one streamed resident launch
-    with arplan.Plan(512, 1 << 14, "bf16", "tree", (8, 8, 8)) as p:
-        p.set_option(arplan.AR_OPT_SLICE, 1)
-        assert p.launch_kernels() == ["stream_kernel"], p.launch_kernels()
+    # n > 64 with AR_OPT_SLICE = 1: one one-pass launch, or (without that) one
+    # streamed resident launch, and n = 8 a resident one
+    for n, N, dtype, kind, fan, kernel in ((512, 1 << 14, "bf16", "tree", (8, 8, 8), "stream_kernel"),
+                                           (8, 1 << 26, "f32", "rhd", None, "resident_kernel")):
+        with arplan.Plan(n, N, dtype, kind, fan) as p:
+            p.set_option(arplan.AR_OPT_SLICE, 1)
+            assert p.launch_kernels() == ["onepass_kernel"], p.launch_kernels()
+            set_onepass(p.handle, 0)
+            assert p.launch_kernels() == [kernel], p.launch_kernels()
     with arplan.Plan(8, 1 << 12, "f32", "rhd") as p:
         with pytest.raises(arplan.ArError):
             arplan.ar_plan_launch_kernel(p.handle, len(p.launches()))
@@ -774,10 +790,10 @@ def test_random_many_destination_plans_split(seed):
         arplan.ar_plan_destroy(h)
 
 
-# The automatic choice (AR_OPT_SLICE = 2) on every benchmark workload: the
-# kernel of each launch.  Each is the fastest form measured on MI355X (or
-# within a few % of it); a change to the cost model that moves one of them
-# shows here first.
+# The automatic choice (AR_OPT_SLICE = 2) on every benchmark workload without
+# the one-pass launch: the kernel of each launch.  Each is the fastest of these
+# forms measured on MI355X (or within a few % of it); a change to the cost model
+# that moves one of them shows here first.
 BENCH_CHOICE = {
     "ring_n4_f32": ["resident_kernel"],
     "ring_n4_i32": ["resident_kernel"],
@@ -803,15 +819,24 @@ BENCH_CHOICE = {
 }
 
 
+# The workloads that run one-pass instead, in one launch of teams or waves; the
+# others run as above.
+BENCH_ONE_PASS = {"rhd_n8_f32", "sweep_ring_n64_f32_N4096", "sweep_ring_n64_bf16_N4096",
+                  "sweep_ring_n64_f32_N1048576", "sweep_ring_n64_bf16_N1048576",
+                  "sweep_tree8x8_n64_f32_N1048576", "sweep_tree8x8_n64_bf16_N1048576"}
+
+
 def test_automatic_choice_beyond_64_buffers():
-    # Ring over 128 and 256 buffers runs as one streamed launch up to the
-    # sizes where it was measured faster; RHD's 128-destination phase of
-    # 128-byte steps runs split, outside the sliced run; trees and large
-    # Rings keep their launches
-    def kernels(kind, n, N, dtype, fan=None):
+    # Ring over 128 and 256 buffers runs one-pass, without that as one streamed
+    # launch up to the sizes where it was measured faster; RHD's
+    # 128-destination phase of 128-byte steps runs split, outside the sliced
+    # run; trees and large Rings keep their launches
+    def kernels(kind, n, N, dtype, fan=None, onepass=0):
         with arplan.Plan(n, N, dtype, kind, fan) as p:
+            set_onepass(p.handle, onepass)
             return p.launch_kernels()
     for n, N, dtype in [(128, 1 << 12, "f32"), (256, 1 << 15, "f32"), (128, 1 << 18, "bf16")]:
+        assert kernels("ring", n, N, dtype, onepass=1) == ["onepass_kernel"], (n, N, dtype)
         assert kernels("ring", n, N, dtype) == ["stream_kernel"], (n, N, dtype)
     assert "stream_kernel" not in kernels("ring", 128, 1 << 20, "f32")
     k = kernels("rhd", 128, 1 << 12, "f32")
@@ -830,6 +855,9 @@ def test_automatic_choice_of_bench_workloads(name):
     from paper_2409_04202_amd import workloads
     c = workloads.CONFIGS[name]
     with arplan.Plan(c["n"], c["N"], c["dtype"], c["kind"], c["fanin"]) as p:
+        assert p.launch_kernels() == (["onepass_kernel"] if name in BENCH_ONE_PASS
+                                      else BENCH_CHOICE[name])
+        set_onepass(p.handle, 0)
         assert p.launch_kernels() == BENCH_CHOICE[name]
 
 

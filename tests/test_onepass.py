@@ -18,7 +18,7 @@ import torch
 import oracle
 from paper_2409_04202_amd import workloads
 
-from checklib import arplan as check
+from checklib import arplan as check, set_onepass
 from test_capi_host import _check_tiling
 
 if torch.cuda.is_available():
@@ -45,10 +45,10 @@ def test_program_and_tiles(kind, n, fan, dtype):
               4608 * kib + 1, 7168 * kib + 5):
         with check.Plan(n, N, dtype, kind, fan) as p:
             L = p.launches()
-            if n <= 512 and N % n:
+            if n <= 512 and (N % n if kind != "rb" else N * es % 16):
                 # a step boundary off 16 bytes: one launch moving each byte once
-                assert [x[0] for x in L] == [-2] and L[0][4] == 2 * n * N * es, (N, L)
-                assert p.launch_kernels() == ["resident_kernel"]
+                assert [x[0] for x in L] == [-4] and L[0][4] == 2 * n * N * es, (N, L)
+                assert p.launch_kernels() == ["onepass_kernel"]
             for fuse in (1, 0):
                 p.set_option(check.AR_OPT_FUSE, fuse)
                 for vecok in (1, 0):
@@ -57,6 +57,9 @@ def test_program_and_tiles(kind, n, fan, dtype):
             # not without resident launches, nor without sliced ones
             p.set_option(check.AR_OPT_RESIDENT, 0)
             assert all(x[0] >= -1 for x in p.launches())
+            p.set_option(check.AR_OPT_RESIDENT, 1)
+            set_onepass(p.handle, 0)
+            assert "onepass_kernel" not in p.launch_kernels()
 
 
 def test_plans_that_have_no_one_pass_form():

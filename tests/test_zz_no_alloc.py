@@ -133,18 +133,21 @@ def test_no_device_memory_is_allocated():
 
 
 def test_too_large_is_refused_before_any_launch():
-    # RHD n = 8 at 2^28 fp32 runs as one resident launch with 2^20
-    # workgroups: 40 MiB of unit records, more than the array holds.  Real
-    # buffers, so that nothing could touch memory it does not own.
+    # RHD n = 8 at 2^28 fp32 as one resident launch has 2^20 workgroups: 40 MiB
+    # of unit records, more than the array holds.  The limit holds for these
+    # tables where a one-pass launch takes its place, too.  Real buffers, so
+    # that nothing could touch memory it does not own.
     n, N = 8, 1 << 28
-    with arplan.Plan(n, N, "f32", "rhd") as p:
-        assert [x[0] for x in p.launches()] == [-2]
-        bufs = [torch.empty(N, dtype=torch.float32, device="cuda") for _ in range(n)]
-        with pytest.raises(arplan.ArError) as e:
-            p.execute_noalloc(bufs)
-        assert e.value.status == arplan.AR_ERR_UNSUPPORTED
-        assert str(arplan.AR_NOALLOC_MAX_BYTES) in str(e.value)
-        del bufs
+    bufs = [torch.empty(N, dtype=torch.float32, device="cuda") for _ in range(n)]
+    for onepass in (1, 0):
+        with check.Plan(n, N, "f32", "rhd") as p:
+            set_onepass(p.handle, onepass)
+            assert [x[0] for x in p.launches()] == [-4 if onepass else -2]
+            with pytest.raises(check.ArError) as e:
+                p.execute_noalloc(bufs)
+            assert e.value.status == check.AR_ERR_UNSUPPORTED
+            assert str(check.AR_NOALLOC_MAX_BYTES) in str(e.value)
+    del bufs
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
 
