@@ -179,15 +179,6 @@ static std::string check_streamed(const ar_plan& plan, const ExecState& ex, cons
     return "";
 }
 
-// Host-side check of the executed phases and the launch tiling (no GPU):
-// every executed phase is free of hazards, and walking every wave tile of
-// every launch with the kernel's own index helpers covers each step exactly
-// once, in bounds, with 16-byte aligned vector parts (the padding entries of
-// a tile table excepted, which the kernel skips).  In a split launch the
-// waves of a workgroup share one tile, and their shares of a step's
-// destinations cover each destination once, the ones among the step's
-// sources (stored after the barrier) last.  An affinity table puts every
-// tile on the XCD (workgroup id modulo kNumXCDs) that xcd_of names.
 // Check of the one-pass form (onepass_kernel): per segment, running its leaves
 // on terms (an input row, an unordered 2-operand add, for bf16 the rounding at
 // the end of a fold) with the sums put aside gives the term that the executed
@@ -310,6 +301,15 @@ static std::string check_onepass(const ar_plan& plan, const ExecState& ex) {
     return "";
 }
 
+// Host-side check of the executed phases and the launch tiling (no GPU):
+// every executed phase is free of hazards, and walking every wave tile of
+// every launch with the kernel's own index helpers covers each step exactly
+// once, in bounds, with 16-byte aligned vector parts (the padding entries of
+// a tile table excepted, which the kernel skips).  In a split launch the
+// waves of a workgroup share one tile, and their shares of a step's
+// destinations cover each destination once, the ones among the step's
+// sources (stored after the barrier) last.  An affinity table puts every
+// tile on the XCD (workgroup id modulo kNumXCDs) that xcd_of names.
 AR_EXPORT ar_status ar_debug_check_tiling(ar_plan* plan, int32_t vecok,
                                           char* msg, int64_t msglen) {
     clear_error();

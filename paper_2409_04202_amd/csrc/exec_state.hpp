@@ -258,7 +258,7 @@ constexpr int64_t kOneMaxWork = int64_t(1) << 22;
 // bytes.
 constexpr int64_t kOneNarrowTiles = 512;
 // Launches of more tiles than kOneManyTiles run in many rounds: tile after
-// tile, and with LDS asked for that nothing uses (kOneStreamLds), so that 20
+// tile, and with LDS asked for that nothing uses (one_lds), so that 20
 // (n = 2), 16 (n = 4 to 7) or 12 (n >= 8) wavefronts run on a compute unit.
 // us, an eighth of the tiles on each XCD and no limit / tile after tile and
 // 12 / 16 / 20: n = 4 fp32 over 2^26 364 / 364 / 341 / 338, over 2^27 724 /
@@ -305,9 +305,10 @@ constexpr double kOneOverlap = 0.2;
 // place of several launches when predicted at most kOneGain of their time: the
 // two predictions are off by up to a fifth each (over buffer sets in turn
 // the launches' is low: the (8, 8) tree over 2^20 fp32 139 us, predicted 85),
-// and only where its bytes take the longer time: the choice for short plans is
-// pinned by the tests (some would gain: RHD n = 128 over 2^12 fp32, split
-// launches, 25 us, teams 12.5).
+// and only where its bytes take the longer time: of shorter plans too few were
+// timed to say where it is the faster (RHD n = 128 over 2^12 fp32 takes 25 us by
+// its launches and 12.5 by teams, the (8, 8) tree over 2^16, two launches, 9.2,
+// Ring n = 64 over 65541 one-pass 10.9).
 // Otherwise no phases can share a launch and each does its steps' ends or, on
 // unaligned buffers, everything element-wise, so it does so always up to
 // kOneFreeN buffers.  Measured on 167 plans with n = 5 to 512 over 1003 to

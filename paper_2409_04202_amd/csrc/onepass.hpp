@@ -56,9 +56,10 @@ namespace arp {
 //    step and end together), with as many leaves in a batch as n gives it
 //    registers for no more (n = 3 over 2000003 fp32: B 4 9.0 us, B 16 11.3;
 //    RHD n = 8 over 2^26: B 8 716, B 4 743);
-//  * LB 16, U 4, 8 (bf16) or 16 where that still makes 512 to 2048 wavefronts:
-//    the whole launch is then resident at once, so that the chip first reads and
-//    then writes, and each buffer is touched in 4 or 16 KiB pieces (Ring
+//  * LB 16, U 4, 8 or 16 where that still makes 448 to 2048 wavefronts
+//    (kOneWide): the whole launch is then resident at once, so that the chip
+//    first reads and then writes, and each buffer is touched in 4, 8 or 16 KiB
+//    pieces (Ring
 //    n = 64 over 2^20 fp32: U 1 97 us, U 4 91; tree (8, 8) over 2^22: U 1
 //    386, U 16 357; bf16, whose sums take twice the registers, U 1 192, U 8
 //    187, U 16 209).  Larger ones run in many rounds anyhow and stream best
@@ -274,8 +275,9 @@ struct OnePass {
 // segment's end do nothing).  ptab: the n buffer pointers.  CM: bit 0
 // nontemporal loads, bit 1 nontemporal stores.  The grid is 8 * per_xcd:
 // workgroups go to the eight XCDs in turn, and each runs a contiguous eighth
-// of the tiles; per_xcd = 0: tile after tile, whatever the XCD.  (per_xcd is an argument: a kernel that reads gridDim takes
-// the 256 bytes of implicit arguments, 1 us more a launch on the host.)
+// of the tiles; per_xcd = 0: tile after tile, whatever the XCD.  (per_xcd is an
+// argument: a kernel that reads gridDim takes the 256 bytes of implicit
+// arguments, 1 us more a launch on the host.)
 template <int DT, int LB, int U, int B, int W, int CM>
 __global__ __launch_bounds__(64 * W) void onepass_kernel(
     const uint64_t* __restrict__ ptab, int32_t n, const uint32_t* __restrict__ prog,

@@ -545,9 +545,9 @@ static double stream_time(const Plan& p, const SliceDesc& sd) {
 
 // What a whole-plan streamed launch takes at least, for the built-in kinds: a
 // program loads every buffer's row (a word each) and stores every buffer (half
-// a word each), with kStreamAhead rows in LDS where there are so many.  Building the programs
-// only to price them took most of the first call of the (8, 8, 8) tree over
-// 512 buffers (26 ms).
+// a word each), with kStreamAhead rows in LDS where there are so many.  Building
+// the programs only to price them took most of the first call of the (8, 8, 8)
+// tree over 512 buffers (24 ms, 8 without).
 static double stream_bound(const Plan& p) {
     if (p.kind < 0) return 0.0;  // a custom plan may touch few buffers
     const int64_t words = int64_t(p.n) + p.n / 2;
@@ -631,12 +631,13 @@ ExecState* exec_state(Plan& p) {
                 if (r.a == 0 && r.b == P && one_may) {
                     const bool by_time = sd.streamed || (p.slice == 2 && onepass_teams(p));
                     const double t = sd.streamed ? stream_time(p, sd) : t_whole;
-                    if (by_time)
+                    if (by_time) {
                         ex->one_aligned = onepass_time(p, ex->one) < t && one_time() < t;
-                    else
-                        ex->one_aligned = onepass_streams(p, ex->one) && one_time() >= 0.0 &&
-                                          ex->one.ok && onepass_streams(p, ex->one) &&
+                    } else if (onepass_streams(p, ex->one)) {  // it may: build it to say
+                        build_onepass(p, *ex, ex->one);
+                        ex->one_aligned = ex->one.ok && onepass_streams(p, ex->one) &&
                                           (!sd.resident || onepass_beats_rows(p, ex->one));
+                    }
                 }
                 sd.cuts_base = ex->slices.empty() ? 0
                                                   : ex->slices.back().cuts_base +
