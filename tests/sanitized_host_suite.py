@@ -2,7 +2,7 @@
 
 Builds ``lib/libarplan_check_san.so`` (``build.build_sanitized``: the test
 library with its host code -- plan expansion, the C ABI, the executor's
-rewrites, launch planning, resident programs, GenModel and the checking
+rewrites, launch planning, resident and one-pass programs, GenModel and the checking
 hooks -- under AddressSanitizer and UndefinedBehaviorSanitizer, any
 undefined behaviour fatal), then runs the host test files that drive that
 code, through ``tests/checklib.py`` and, via ``ARPLAN_LIB``, the product
@@ -22,7 +22,8 @@ sys.path.insert(0, ROOT)
 from paper_2409_04202_amd import build  # noqa: E402
 
 HOST_FILES = ["tests/test_capi_host.py", "tests/test_exec_rewrites_host.py",
-              "tests/test_resident_host.py", "tests/test_genmodel_host.py"]
+              "tests/test_resident_host.py", "tests/test_genmodel_host.py",
+              "tests/test_onepass.py"]
 
 
 def main(argv):

@@ -188,6 +188,34 @@ def test_dense_rows_leave_their_surroundings_alone(dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("pad", [0, 1])
+@pytest.mark.parametrize("n,N,slice_", [(8, 8 * 4096, 2), (12, 4099, 2), (12, 4099, 0)])
+def test_timer_records_one_launch_or_one_a_phase(n, N, slice_, pad):
+    # one record an execution where it runs one-pass: on buffers off 16 bytes,
+    # and wherever a step boundary is; one a phase launch without
+    xs0 = workloads.draw(n, N, "f32", "uniform", 9)
+    want = oracle.execute(oracle.rhd(n, N), [x.copy() for x in xs0], "f32")
+    t = arplan.ar_timer_create(64)
+    try:
+        with arplan.Plan(n, N, "f32", "rhd") as p:
+            p.set_option(arplan.AR_OPT_SLICE, slice_)
+            L = p.launches()
+            one = slice_ == 2 and (pad or p.launch_kernels() == ["onepass_kernel"])
+            say("case: timed rhd n=%d N=%d slice=%d pad=%d" % (n, N, slice_, pad))
+            for rep in range(2):
+                ts = to_device(xs0, "f32", pad)
+                p.execute_timed(ts, torch.cuda.current_stream(), t)
+                torch.cuda.synchronize()
+                got = to_host(ts, "f32")
+                assert all(np.array_equal(got[q], want[q]) for q in range(n))
+            recs = arplan.ar_timer_read(t, 64)
+            assert [li for li, _ in recs] == (list(range(1 if one else len(L))) * 2)
+            assert all(ms > 0 for _, ms in recs)
+    finally:
+        arplan.ar_timer_destroy(t)
+
+
+@pytest.mark.gpu
 def test_many_plans_share_the_no_allocation_array():
     # 20 plans of 2 MiB of records each (Ring over 128 buffers as written)
     # in turn: their images go round the 32 MiB array; a graph of the first
