@@ -33,10 +33,14 @@ Prints one JSON line.  The headline (RHD, n = 8, N = 2^26 fp32):
               buffer tile once in and once out: 2 * n * N * e)
   cpu_baseline  the CPU oracle executing the same plan on the host
   configs     every workload (each config of the scope, the GenTree
-              topologies and the n = 64 sweep) in both forms, each with a
-              bounded CPU oracle baseline; a form whose K executions take
-              less than 5 ms is timed over enough executions for about 5 ms
-              (`timed_steps`)
+              topologies and the n = 64 sweep): per form the step time in ms,
+              the algorithm bandwidth and the reduce launches' throughput in
+              GB/s, their fraction of the HBM peak and the kernels
+              (`configs_fields`), and the GB/s of a bounded CPU oracle
+              baseline; a form whose K executions take less than 5 ms is
+              timed over enough executions for about 5 ms.  The line stays
+              short so that a log's tail holds all of it; `--details FILE`
+              writes every workload's launches and baselines beside it
 and, beside those: the step time's median and minimum over individually
 timed executions, a practical ceiling measured in the same run (a device
 copy with torch and with the library, a two-source fold through the
@@ -68,8 +72,8 @@ def _code_only(text):
     return " ".join(text.split())
 
 
-KERNEL_SOURCES = ("kernels.hpp", "resident.hpp", "exec.hip", "exec_state.hpp", "rewrite.cpp",
-                  "schedule.cpp", "programs.cpp")
+KERNEL_SOURCES = ("kernels.hpp", "resident.hpp", "onepass.hpp", "exec.hip", "exec_state.hpp",
+                  "rewrite.cpp", "schedule.cpp", "programs.cpp", "onepass.cpp")
 
 
 def kernel_source_hash():
@@ -468,7 +472,22 @@ def headline_line(h, K, W, name):
     return out
 
 
+CONFIGS_FIELDS = ("ms_per_step", "algbw_gbs", "reduce_gbs", "reduce_frac", "kernels")
+
+
+def config_short(r):
+    """A workload's entry in the printed line (CONFIGS_FIELDS per form)."""
+    e = {"workload": r["workload"]}
+    for form in FORMS:
+        if form in r:
+            f = r[form]
+            e[form] = [f[k] for k in CONFIGS_FIELDS[:-1]] + ["+".join(f["kernels"])]
+    e["oracle_gbs"] = (r.get("cpu_baseline") or {}).get("value")
+    return e
+
+
 def config_entry(r):
+    """... and in the details file."""
     e = {k: r[k] for k in ("workload", "plan", "n", "N", "dtype", "fanin")}
     for form in FORMS:
         if form in r:
@@ -506,6 +525,8 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-ceiling", action="store_true",
                     help="skip the copy / two-source fold ceiling measurement")
+    ap.add_argument("--details", metavar="FILE",
+                    help="write every workload's launches and baselines as JSON")
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
         print("bench.py: the library executes every emulated processor on one "
@@ -535,14 +556,20 @@ def main():
     h = bench_workload(torch, arplan, args.config, K, W, forms, stream,
                        10.0 if cpu else 0.0, headline=True)
     out = headline_line(h, K, W, args.config)
+    details = [config_entry(h)]
     if not args.no_configs:
-        out["configs"] = [config_entry(h)]
+        out["configs_fields"] = CONFIGS_FIELDS
+        out["configs"] = [config_short(h)]
         for name in workloads.CONFIGS:
             if name == args.config:
                 continue
             r = bench_workload(torch, arplan, name, K, W, forms, stream,
                                1.5 if cpu else 0.0, min_ms=5.0)
-            out["configs"].append(config_entry(r))
+            out["configs"].append(config_short(r))
+            details.append(config_entry(r))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(details, f, indent=1)
     if not args.no_ceiling:
         print("bench: practical ceiling", file=sys.stderr, flush=True)
         out["ceiling"] = ceiling(torch, arplan)

@@ -1,6 +1,7 @@
 """Host-side checks of bench.py: the multi-GPU refusal and the thread-pool
 form of the oracle used for the parallel CPU baseline."""
 
+import json
 import os
 import subprocess
 import sys
@@ -53,9 +54,39 @@ def test_kernel_source_hash_ignores_comments_only():
     assert bench._code_only(a) != bench._code_only(c)
     # the stripping assumes no string literal holds a comment marker
     csrc = os.path.join(ROOT, "paper_2409_04202_amd", "csrc")
-    for f in ("kernels.hpp", "resident.hpp", "exec.hip", "exec_state.hpp", "rewrite.cpp",
-              "schedule.cpp", "programs.cpp"):
+    # (every file of the executor but the test hooks; the plan library, which
+    # decides the steps and not their launches, is not among them)
+    assert set(bench.KERNEL_SOURCES) == {f for f in os.listdir(csrc)
+                                         if f.endswith((".hpp", ".hip", ".cpp"))} - {
+        "debug.cpp", "capi.cpp", "genmodel.cpp", "internal.hpp", "plan.cpp", "plan.hpp"}
+    for f in bench.KERNEL_SOURCES:
         for line in open(os.path.join(csrc, f)):
             code = line.split("//")[0]
             for lit in code.split('"')[1::2]:
                 assert "//" not in lit and "/*" not in lit, (f, line)
+
+
+def test_line_stays_short():
+    # the printed line with every workload in it, from results of the largest
+    # plausible width: a log's tail has to hold it
+    form = {"ms_per_step": 12.34567, "timed_steps": 4000, "algbw_gbs": 12345.67,
+            "plan_gbs": 12345.6, "kernel_ms_per_step": 12.34567, "reduce_launches": 6,
+            "reduce_bytes": 1 << 40, "reduce_ms": 12.34567, "reduce_gbs": 12345.6,
+            "reduce_frac": 0.1234, "copy_gbs": 12345.6,
+            "kernels": ["phase_kernel", "sliced_kernel", "split_kernel"],
+            "launches": [{"phase": 5, "k": 16, "max_dst": 64, "steps": 4032, "bytes": 1 << 40,
+                          "ms": 12.34567, "gbs": 12345.6}] * 6,
+            "_plan_bytes": (1 << 40, 1 << 40), "_red": [(0, 2, 1 << 40, 1.0)] * 3}
+    base = {"value": 12.3456, "unit": "GB/s", "cores": 1, "kind": "oracle", "sample": "x" * 90,
+            "cpu": "x" * 40, "seconds": 12.345}
+    res = [{"workload": name, "plan": c["kind"], "n": c["n"], "N": c["N"], "dtype": c["dtype"],
+            "fanin": None, "default": form, "as_written": form, "cpu_baseline": base,
+            "cpu_parallel": base, "step_ms": {"median": 12.34567, "min": 12.34567}}
+           for name, c in workloads.CONFIGS.items()]
+    out = bench.headline_line(res[0], 20, 5, bench.HEADLINE)
+    out["configs_fields"] = bench.CONFIGS_FIELDS
+    out["configs"] = [bench.config_short(r) for r in res]
+    out["ceiling"] = {"copy_gbs": 12345.6, "copy_lib_gbs": 12345.6, "fold2_gbs": 12345.6}
+    assert len(json.dumps(out)) < 10000
+    assert [e["workload"] for e in out["configs"]] == list(workloads.CONFIGS)
+    assert all("launches" in bench.config_entry(r)["default"] for r in res)
