@@ -49,12 +49,13 @@ constexpr int64_t kWideBytes = int64_t(512) << 20;
 // A launch below kNtBytes stays in the caches and is bound by latency: more
 // wavefronts in flight, with the registers of fewer vectors, serve it better.
 // Its copies make passes of kNarrowU1 vectors a lane, and its runtime-source-
-// count folds of kNarrowMinSrc and more sources passes of kNarrowU0.  us, as
-// written, fp32 unless said: co-located PS n = 12 over 2^16 10.6 -> 9.7, n = 24
-// over 2^18 25.0 -> 20.1, n = 32 over 2^18 33.4 -> 28.1, n = 24 bf16 over 2^20
-// 37.7 -> 35.3, n = 12 over 2^20 37.0 -> 36.5; copies alone: RHD n = 8 over
-// 2^20 31.2 -> 30.0, Ring n = 16 over 2^22 280 -> 266, the (8, 8) tree over 2^18
-// 34.8 -> 35.1.
+// count folds of kNarrowMinSrc and more sources passes of kNarrowU0 where one
+// pass covers what a wavefront has of a step.  Launches alone, narrow against
+// wide, geometric mean over random ones: copies 0.97 (up to 1 MiB), 0.91 (1 to 4
+// MiB), 0.90 (8 to 64 MiB), 1 in 40 slower by over 3 %; folds over tiles or steps
+// of up to two vectors a lane 0.81, 1 in 500 slower; over longer ones, where it is
+// two dependent passes to one, 1.21 (co-located PS n = 12 as written over 50805
+// bf16 16.0 -> 19.3 us).
 // Folds of 6 sources lost (9.2 -> 9.5 at 2^16 fp32, 25.9 -> 27.9 at 2^22
 // bf16), and so did larger launches of either kind, which stream (RHD n = 8
 // over 2^26 1496 -> 1567, co-located PS n = 32 over 2^22 172 -> 205), also with
@@ -257,15 +258,28 @@ constexpr int64_t kOneMaxWork = int64_t(1) << 22;
 // Tiles of 64 16-byte vectors (1 KiB of a buffer) up to which lanes take 4
 // bytes.
 constexpr int64_t kOneNarrowTiles = 512;
-// Launches of more tiles than kOneManyTiles run in many rounds: tile after
-// tile, and with LDS asked for that nothing uses (one_lds), so that 20
-// (n = 2), 16 (n = 4 to 7) or 12 (n >= 8) wavefronts run on a compute unit.
+// Launches of more tiles than kOneManyTiles, one vector a lane, run in many
+// rounds: tile after tile, and with LDS asked for that nothing uses (one_lds), so
+// that 16 (n = 4 to 7) or 12 (n >= 8) wavefronts run on a compute unit.
 // us, an eighth of the tiles on each XCD and no limit / tile after tile and
 // 12 / 16 / 20: n = 4 fp32 over 2^26 364 / 364 / 341 / 338, over 2^27 724 /
 // 714 / 675 / 673; n = 6 over 43690368 (XCDs and 12: 358) / 339 / 325 / 331;
 // n = 8 over 2^25 362 / 349 / 355 / 360, over 2^26 725 / 712 / 736 / 744;
 // n = 3 over 89478336 361 / 465 / 377 / 357, no limit 334; n = 8 over 2^23,
-// 32768 tiles, 94 / 96 / 102 / 103.
+// 32768 tiles, 94 / 96 / 102 / 103.  Two buffers never gain (of the time of the
+// launch that one-pass takes the place of, over 192 to 384 MiB in all, an eighth on
+// each XCD 0.90, tile after tile 0.94).
+// With fewer than kOneFewN buffers, all on 16 bytes as every segment is, so do
+// launches of half as many tiles that are kOneFewBytes and more in all, and of any
+// number up to kOneFewBytesTo, which the last-level cache holds in part.  Of the
+// time of the launch that it takes the place of, an eighth on each XCD / tile after
+// tile, about 20 plans each: n = 6 over 160 to 192 MiB 0.92 / 0.81, n = 7 over 128
+// to 256 MiB 0.93 / 0.86, n = 9 over 160 to 256 0.90 / 0.82; n = 5 over 80 to 96
+// MiB 1.06 / 1.01, n = 6 0.99 / 0.94, n = 8 1.01 / 0.97, n = 7 over 96 to 112 1.10 /
+// 1.03; but n = 8 over 112 to 128 MiB (up to 16384 tiles) 0.79 / 0.90, n = 4 over 48
+// to 80 MiB 0.90 / 0.93.  Off 16 bytes the tiles' first and last cache lines are
+// their neighbours' too, which then run on other XCDs: Ring n = 6 over 8000003
+// int32 75 / 85 us, the (2, 2) tree over rows of 8099744 fp32 off 16 bytes 52 / 57.
 constexpr int64_t kOneManyTiles = 32768;
 constexpr int32_t one_lds(int32_t n) { return n == 2 ? 8192 : n == 3 ? 0 : n < 8 ? 10240 : 13312; }
 // Of kOneTeamMinN buffers and more, those up to which a workgroup takes a tile

@@ -225,7 +225,9 @@ static void build_launches(const Plan& p, ExecState& ex) {
                 if (written > keep || !next_reads_output) L.cm |= 2;
             }
             L.narrow = bytes < kNtBytes &&
-                       (L.kern_k == 1 || (L.kern_k == 0 && k >= kNarrowMinSrc));
+                       (L.kern_k == 1 ||
+                        (L.kern_k == 0 && k >= kNarrowMinSrc &&
+                         std::min(te, maxspan) <= int64_t(64) * kNarrowU0 * VEC));
             L.wide = (L.kern_k == 2 && L.cm == 3 && bytes >= kWideBytes &&
                       maxdst < kSplitMinDst && te == int64_t(64) * kWideU * VEC &&
                       te == int64_t(cfg.TE) * VEC) ||

@@ -692,18 +692,24 @@ def test_launch_kernels_by_form():
     ("tree", 64, 1 << 23, "f32", (8, 8), 1), ("tree", 64, 1 << 23, "bf16", (8, 8), 0),
     ("tree", 96, 96 * 21840, "f32", (8, 12), 1), ("tree", 96, 96 * 43680, "bf16", (8, 12), 1),
     ("cps", 12, 1 << 18, "f32", None, 0), ("cps", 12, 1 << 22, "f32", None, 0),
+    ("cps", 12, 50805, "bf16", None, 0), ("cps", 12, 12 * 128 * 8, "bf16", None, 0),
+    ("cps", 12, 12 * 136 * 8, "bf16", None, 0), ("rb", 12, 5088, "f32", None, 0),
     ("cps", 6, 1 << 18, "f32", None, 0), ("rhd", 8, 1 << 20, "i32", None, 0)])
-def test_narrow_passes_only_below_64_mib(kind, n, N, dtype, fan, fuse):
-    # copies, and folds of 8 and more sources without an unrolled kernel, take
-    # few vectors a lane in launches of less than 64 MiB; larger ones do not,
-    # cached (cm 0) as they may be: the first four plans have such launches
+def test_narrow_passes_only_where_faster(kind, n, N, dtype, fan, fuse):
+    # copies, and folds of 8 and more sources without an unrolled kernel whose
+    # tiles or steps one narrow pass covers, take few vectors a lane in launches
+    # of less than 64 MiB; larger ones do not, cached (cm 0) as they may be: the
+    # first four plans have such launches
+    pass_ = 128 * (8 if dtype == "bf16" else 4)
     with arplan.Plan(n, N, dtype, kind, fan) as p:
         p.set_option(arplan.AR_OPT_FUSE, fuse)
         p.set_option(arplan.AR_OPT_SLICE, 0)
         L = p.launches()
         d = [_launch_desc(p.handle, i) for i in range(len(L))]
         for x, y in zip(L, d):
-            kinds = y["k"] == 1 or (y["k"] == 0 and x[1] >= 8)
+            step = N if kind == "rb" else -(-N // n)
+            kinds = y["k"] == 1 or (y["k"] == 0 and x[1] >= 8 and
+                                    (y["tile"] <= pass_ or step <= pass_))
             assert y["narrow"] == int(kinds and x[4] < 64 << 20), (x, y)
         if kind == "tree":
             assert any(y["k"] in (0, 1) and y["cm"] == 0 and x[4] >= 64 << 20
