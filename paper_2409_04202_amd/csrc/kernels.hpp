@@ -658,7 +658,15 @@ __global__ __launch_bounds__(64 * kcfg(K).WPB) void phase_kernel(
 // co-located PS n = 16 over 1048581 fp32 50 -> 31, bf16 84 -> 31; RHD n = 8 over
 // 4194309 fp32 171 -> 106, bf16 190 -> 60, over 131075 bf16 149 -> 22; the
 // (8, 8) tree over 4194309 fp32 925 -> 598.
+// A remainder takes an element-wise pass beside the vectors', so a tile of up to
+// kAnyScalar elements (one a lane) that has one takes that pass alone, which
+// covers it (co-located PS n = 128 over 6270 fp32, 49 elements a step, 57 us and
+// with vectors 82; the (16, 12) tree over 843 int32 33 and 44).  Longer ones
+// gain by vectors, since the pass waits for its elements a lane one after the
+// other (n = 8 rows of 238531 fp32 into one and back 5.3 us, element-wise up to
+// 256 elements 7.9).
 constexpr int kAnyU = 4;  // vectors per lane and source of a pass, 2 from 8 sources on
+constexpr int64_t kAnyScalar = 64;
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 template <int DT> struct AnyVec { using M = u32x4_a4; };
@@ -757,7 +765,8 @@ __global__ __launch_bounds__(64 * kcfg(K).WPB) void phase_any_kernel(
     // elements [lo, hi) of the step; whole vectors from lo, then the rest
     const TileSpan ts = tile_span(st.begin, st.end, t, tile_elems, VEC, false);
     if (ts.lo >= ts.hi) return;
-    const int64_t nv = (ts.hi - ts.lo) / VEC;
+    const int64_t len = ts.hi - ts.lo;
+    const int64_t nv = len <= kAnyScalar && len % VEC ? 0 : len / VEC;
     int64_t at = 0;
     for (; at + 64 * U <= nv; at += 64 * U)
         fold_any<DT, K, U, true>(sp, k, dp, st.ndst, ts.lo + at * VEC, 64 * U, lane);

@@ -288,7 +288,9 @@ def test_phase_launches_on_element_aligned_buffers(n, dtype):
     # with the rewrites (many destinations); around a pass of 64 lanes x 2 or 4
     # vectors and a tile
     vec = 8 if dtype == "bf16" else 4
-    for N in (n + 1, 64 * vec * 2 * n + 1, 64 * vec * 4 * n - 1, 1024 * vec * n + 5):
+    # and about the steps of up to 64 elements with a remainder
+    for N in (n + 1, 64 * vec * 2 * n + 1, 64 * vec * 4 * n - 1, 1024 * vec * n + 5,
+              49 * n, 61 * n + 1, 64 * n - 1, 65 * n):
         xs0 = workloads.draw(n, N, dtype, "int1000" if dtype == "i32" else "uniform", N % 97)
         want = oracle.execute(oracle.make_plan("cps", n, N, None), [x.copy() for x in xs0], dtype)
         for fuse in (0, 1):
