@@ -390,7 +390,7 @@ struct DevView {
 template <int DT, int LB, int U, int B, int W>
 static void launch_one(const Plan& p, const OnePlan& one, const DevView& v, hipStream_t stream) {
     const int64_t blocks = (one.nunits + W - 1) / W;
-    const bool many = U == 1 && W == 1 && one.many;
+    const bool many = U == 1 && W == 1 && one.many >= (v.align == ALIGN_16 ? 1 : 2);
     const uint32_t per_xcd = many ? 0u : static_cast<uint32_t>((blocks + 7) / 8);
     const dim3 grid(many ? static_cast<uint32_t>(blocks) : per_xcd * 8), block(64 * W);
     const size_t lds = std::max(size_t(one.depth) * U * 64 * W * sizeof(typename OneVec<DT, LB>::Acc),

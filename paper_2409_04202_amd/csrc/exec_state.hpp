@@ -281,7 +281,11 @@ constexpr int64_t kOneNarrowTiles = 512;
 // their neighbours' too, which then run on other XCDs: Ring n = 6 over 8000003
 // int32 75 / 85 us, the (2, 2) tree over rows of 8099744 fp32 off 16 bytes 52 / 57.
 constexpr int64_t kOneManyTiles = 32768;
-constexpr int32_t one_lds(int32_t n) { return n == 2 ? 8192 : n == 3 ? 0 : n < 8 ? 10240 : 13312; }
+constexpr int32_t kOneManyMinN = 3;
+constexpr int32_t kOneFewN = 12;
+constexpr int64_t kOneFewBytes = int64_t(80) << 20;
+constexpr int64_t kOneFewBytesTo = int64_t(112) << 20;
+constexpr int32_t one_lds(int32_t n) { return n == 3 ? 0 : n < 8 ? 10240 : 13312; }
 // Of kOneTeamMinN buffers and more, those up to which a workgroup takes a tile
 // of 4-byte lanes (onepass_team_kernel): of 16 waves while each compute unit
 // has one such tile (half as many again for kOneTeamManyN buffers), else of
@@ -293,6 +297,11 @@ constexpr int32_t one_lds(int32_t n) { return n == 2 ? 8192 : n == 3 ? 0 : n < 8
 constexpr int32_t kOneTeamMinN = 20;
 constexpr int32_t kOneTeamManyN = 128;
 constexpr int64_t kOneTeamTiles = 200;
+// A launch of four-wave teams takes the place of a resident one when predicted
+// below kOneTeam4Gain of its time: of 56 plans predicted at 0.95 to 1.0, Ring
+// n = 23 to 47 for the most part, 16 took longer (0.98 of it on average, up to
+// 1.34: n = 28 fp32 over 28224 5.2 and 7.0 us); of 242 below, 3.
+constexpr double kOneTeam4Gain = 0.95;
 constexpr int64_t kOneTeam16Tiles = 64;
 // n * N * e from which a one-pass launch loads and stores nontemporally.
 constexpr int64_t kOneNtBytes = int64_t(96) << 20;
@@ -460,7 +469,8 @@ struct OnePlan {
     bool tried = false;      // built, or found to have none
     bool ok = false;         // every buffer ends with one value at every position
     bool chain = false;      // a chain of bf16 steps
-    bool many = false;       // runs in many rounds (kOneManyTiles)
+    int32_t many = 0;        // tile after tile (kOneManyTiles): 1 on buffers on 16
+                             // bytes, 2 on any
     int32_t pushes = 0;      // most sums put aside in a segment
     OneConf conf{};
     int32_t depth = 0;       // sums put aside at once
@@ -590,14 +600,20 @@ OneConf one_config(int32_t n, int64_t tiles16, int32_t depth, int32_t dtype, boo
 // may.
 double onepass_time(const Plan& p, const OnePlan& one);
 bool onepass_streams(const Plan& p, const OnePlan& one);
-// Is the form faster than the resident one where both stream?  At U 1, below
-// kOneManyTiles and from kOneRowsMinN buffers on (the resident form then has
-// four waves a tile) it is not (RHD n = 32 fp32 over 8388608 resident 372 us,
-// one-pass 395, over 5120000 243 and 257; n = 8 over 8388608 113 and 94, over
-// 8389120 91 and 93).
+// Is the form, where its bytes take the longer time, faster than the whole-plan
+// sliced or resident launch that it would take the place of?  Than a streaming
+// resident one of kOneRowsMinN and more buffers (four waves a tile) not at U 1
+// between half of kOneManyTiles and that many (RHD n = 32 fp32 over 8388608
+// resident 372 us, one-pass 395, over 5120000 243 and 257; n = 8 over 8388608 113
+// and 94, over 8389120 91 and 93).  Than a plain sliced one over two buffers only
+// from kOnePairTiles tiles on and where they fit the caches with room, or it
+// streams: over fewer tiles (2 to 12 MiB a buffer) it takes 0.97 to 1.14 of its
+// time, over 80 to 96 MiB in all 1.11, otherwise 0.90 to 0.97.
 constexpr int32_t kOneRowsMinN = 20;
-bool onepass_beats_rows(const Plan& p, const OnePlan& one);
-// Does the one-pass form of a plan run as teams?
+constexpr int64_t kOnePairTiles = 12288;
+bool onepass_beats_slice(const Plan& p, const OnePlan& one, bool resident);
+// Does the one-pass form of a plan run as teams, and of how many waves?
 bool onepass_teams(const Plan& p);
+int32_t team_waves(const Plan& p);
 
 }  // namespace arp

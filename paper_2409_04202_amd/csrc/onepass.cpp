@@ -106,6 +106,12 @@ static int64_t tiles_of(const Plan& p) {  // of 1 KiB of a buffer
     return (p.N * p.esize + 1023) / 1024;
 }
 bool onepass_teams(const Plan& p) { return team_tiles(p.n, tiles_of(p)); }
+static bool team16(int32_t n, int64_t tiles16) {
+    return tiles16 <= (n >= kOneTeamManyN ? kOneTeam16Tiles * 3 / 2 : kOneTeam16Tiles);
+}
+int32_t team_waves(const Plan& p) {
+    return !onepass_teams(p) ? 0 : team16(p.n, tiles_of(p)) ? 16 : 4;
+}
 // Instance and tile for `tiles16` tiles of 64 16-byte vectors (see
 // onepass.hpp for what was measured).  Instances with U > 1 are for launches
 // that are resident at once, which their wavefronts' registers limit (kOneWide)
@@ -113,10 +119,7 @@ bool onepass_teams(const Plan& p) { return team_tiles(p.n, tiles_of(p)); }
 // depth * U * 64 each.
 OneConf one_config(int32_t n, int64_t tiles16, int32_t depth, int32_t dtype, bool chain) {
     const bool bf16 = dtype == AR_BF16;
-    if (team_tiles(n, tiles16)) {
-        const int64_t one_a_unit = n >= kOneTeamManyN ? kOneTeam16Tiles * 3 / 2 : kOneTeam16Tiles;
-        return {tiles16 <= one_a_unit ? ONE_TEAM16 : ONE_TEAM4, 4, 1, 1};
-    }
+    if (team_tiles(n, tiles16)) return {team16(n, tiles16) ? ONE_TEAM16 : ONE_TEAM4, 4, 1, 1};
     if (tiles16 <= kOneNarrowTiles) return {ONE_LB4, 4, 1, 4};
     if (n >= kOneWideMinN)
         for (const OneWide& w : kOneWide) {
@@ -200,7 +203,14 @@ static void build(const Plan& p, const ExecState& ex, OnePlan& one) {
                                   (w[1] & kOneRound) != 0);
     }
     one.conf = one_config(n, tiles_of(p), one.depth, p.dtype, one.chain);
-    one.many = one.conf.u == 1 && one.conf.lb == 16 && one.cm && tiles_of(p) > kOneManyTiles;
+    if (one.conf.u == 1 && one.conf.lb == 16 && n >= kOneManyMinN) {
+        const int64_t bytes = int64_t(n) * p.N * p.esize;
+        const bool whole = std::all_of(one.segs.begin(), one.segs.end(),
+                                       [&](const OneSeg& sg) { return sg.lo % VEC == 0; });
+        if (one.cm && tiles_of(p) > kOneManyTiles) one.many = 2;
+        else if (whole && n < kOneFewN && bytes >= kOneFewBytes)
+            one.many = tiles_of(p) > kOneManyTiles / 2 || bytes < kOneFewBytesTo;
+    }
     const int64_t vec = one.conf.lb / p.esize;
     const int64_t te = 64 * vec * one.conf.u;
     std::vector<int64_t> nt;
@@ -227,8 +237,8 @@ static void build(const Plan& p, const ExecState& ex, OnePlan& one) {
 void build_onepass(const Plan& p, const ExecState& ex, OnePlan& one) {
     if (one.tried) return;
     one.tried = true;
-    // more than half of the last-level cache: stream past it (n = 64 over
-    // 2^19 fp32, 128 MiB: 46 us, cached 56; over 2^18, 64 MiB: cached 21 us,
+    // more than three eighths of the last-level cache: stream past it (n = 64
+    // over 2^19 fp32, 128 MiB: 46 us, cached 56; over 2^18, 64 MiB: cached 21 us,
     // streamed 23)
     one.cm = int64_t(p.n) * p.N * p.esize >= kOneNtBytes ? 3 : 0;
     one.bytes = 2 * int64_t(p.n) * p.N * p.esize;
@@ -259,9 +269,12 @@ bool onepass_streams(const Plan& p, const OnePlan& one) {
     return one_mem_time(p) >= one_wave_time(p, one);
 }
 
-bool onepass_beats_rows(const Plan& p, const OnePlan& one) {
-    return one.conf.u > 1 || one.conf.lb < 16 || !one.cm || one.many ||
-           p.n < kOneRowsMinN || tiles_of(p) <= kOneManyTiles / 2;
+bool onepass_beats_slice(const Plan& p, const OnePlan& one, bool resident) {
+    const int64_t tiles = tiles_of(p);
+    if (p.n == 2 && !one.cm && !resident)
+        return tiles >= kOnePairTiles && 2 * p.N * p.esize < kOneFewBytes;
+    return !resident || one.conf.u > 1 || one.conf.lb < 16 || !one.cm || one.many ||
+           p.n < kOneRowsMinN || tiles <= kOneManyTiles / 2;
 }
 
 }  // namespace arp

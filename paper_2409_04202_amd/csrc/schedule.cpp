@@ -632,13 +632,15 @@ ExecState* exec_state(Plan& p) {
                 // predicted faster (Ring n = 128 over 2^12 fp32 77 us, 7).
                 if (r.a == 0 && r.b == P && one_may) {
                     const bool by_time = sd.streamed || (p.slice == 2 && onepass_teams(p));
-                    const double t = sd.streamed ? stream_time(p, sd) : t_whole;
+                    const double t = sd.streamed ? stream_time(p, sd)
+                                     : team_waves(p) == 4 ? kOneTeam4Gain * t_whole
+                                                          : t_whole;
                     if (by_time) {
                         ex->one_aligned = onepass_time(p, ex->one) < t && one_time() < t;
                     } else if (onepass_streams(p, ex->one)) {  // it may: build it to say
                         build_onepass(p, *ex, ex->one);
                         ex->one_aligned = ex->one.ok && onepass_streams(p, ex->one) &&
-                                          (!sd.resident || onepass_beats_rows(p, ex->one));
+                                          onepass_beats_slice(p, ex->one, sd.resident);
                     }
                 }
                 sd.cuts_base = ex->slices.empty() ? 0

@@ -62,6 +62,19 @@ def test_program_and_tiles(kind, n, fan, dtype):
             assert "onepass_kernel" not in p.launch_kernels()
 
 
+@pytest.mark.parametrize("kind,n,N,dtype,kernel", [
+    # over two buffers a sliced launch is as fast up to 12 MiB a buffer, and
+    # where both hardly fit the caches; four-wave teams are not where predicted
+    # at over 0.95 of the resident launch's time
+    ("ring", 2, 1 << 21, "f32", "sliced_kernel"), ("rhd", 2, 3633184, "bf16", "sliced_kernel"),
+    ("ring", 2, 11010048, "f32", "sliced_kernel"), ("ring", 2, 1 << 22, "f32", "onepass_kernel"),
+    ("ring", 2, 1 << 24, "f32", "onepass_kernel"), ("ring", 28, 28224, "f32", "resident_kernel"),
+    ("ring", 64, 1 << 15, "f32", "onepass_kernel"), ("rhd", 28, 28224, "f32", "onepass_kernel")])
+def test_where_one_pass_takes_the_place_of_a_launch(kind, n, N, dtype, kernel):
+    with check.Plan(n, N, dtype, kind) as p:
+        assert p.launch_kernels() == [kernel]
+
+
 def test_plans_that_have_no_one_pass_form():
     # buffers that end with different values, positions no step covers, a
     # plain copy (its bits are not to pass through an addition)
@@ -117,7 +130,10 @@ GPU = [("ring", 5, 67, "f32", None), ("rhd", 5, 4099, "f32", None), ("rhd", 7, 4
        ("cps", 12, 3072 * 256 + 5, "f32", None), ("tree", 12, 4608 * 256 + 3, "i32", (4, 3)),
        ("rhd", 12, 7168 * 256 + 9, "f32", None), ("tree", 12, 3100 * 512 + 1, "bf16", (4, 3)),
        ("ring", 13, 4608 * 512 + 7, "bf16", None), ("cps", 12, 7373 * 512 + 3, "bf16", None),
-       ("rhd", 3, 32769 * 256 + 5, "f32", None)]
+       ("rhd", 3, 32769 * 256 + 5, "f32", None),
+       # tile after tile on aligned buffers alone: cached, and from 16384 tiles on
+       ("cps", 6, 14000 * 256, "f32", None), ("rhd", 5, 5 * 4096 * 1024, "bf16", None),
+       ("ring", 7, 7 * 2500 * 256, "i32", None)]
 
 
 def _oracle_plan(kind, n, N, fan):
